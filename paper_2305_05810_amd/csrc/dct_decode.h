@@ -77,4 +77,109 @@ __device__ __forceinline__ float dct_decode_word(uint32_t word, const DctBasis& 
     return f;
 }
 
+// ---------------------------------------------------------------------------
+// Weighted sums of decoded texels by block.
+//
+// A texel is a sum of six products of a coefficient and a function of x and
+// of y, so a tensor-product weighted sum of the texels of one block needs no
+// texel: with S0 = sum wx, S1 = sum wx c1(x), S2 = sum wx c2(x) over the
+// window's columns in the block, and T0..T2 the same over its rows,
+//   sum wx wy f(x, y) = d (T0 S0)/127 + K (q1 T0 S1 + q2 T1 S0 + q3 T2 S0 +
+//                       q5 T0 S2) + K11 q4 T1 S1,
+// six multiply-adds per channel and block instead of a decode per tap.  The
+// taps of a 4x4 window meet 1.9 blocks on average (1, 2 or 4).
+// ---------------------------------------------------------------------------
+
+// The weight sums of the columns (or rows) of a window in one block.
+struct DctAxis {
+    float s0, s1, s2;
+};
+
+// The row sums scaled by the dequantisation steps: one per y block, shared by
+// its x blocks.
+struct DctRow {
+    float dc, k0, k1, k2, k11;
+};
+
+__device__ __forceinline__ DctRow dct_row(const DctAxis& t)
+{
+    return {DCT_DC * t.s0, DCT_K * t.s0, DCT_K * t.s1, DCT_K * t.s2, DCT_K11 * t.s1};
+}
+
+// Factors of the DC code and the five AC codes of every channel of a block
+// (named values: an indexed array here would leave the registers).
+struct DctFactors {
+    float b0, b1, b2, b3, b4, b5;
+};
+
+__device__ __forceinline__ DctFactors dct_factors(const DctRow& r, const DctAxis& s)
+{
+    return {r.dc * s.s0, r.k0 * s.s1, r.k1 * s.s0, r.k2 * s.s0, r.k11 * s.s1, r.k0 * s.s2};
+}
+
+// The six codes of a channel word as binary32 (exact): DC 0..127, AC -15..15.
+struct DctCodes {
+    float c0, c1, c2, c3, c4, c5;
+};
+
+__device__ __forceinline__ DctCodes dct_codes(uint32_t word)
+{
+    const int w = (int)(word ^ 0x84210800u);   // as in dct_decode_word
+    return {(float)(word & 127u),
+            (float)(int)__builtin_amdgcn_sbfe(w, 7, 5),
+            (float)(int)__builtin_amdgcn_sbfe(w, 12, 5),
+            (float)(int)__builtin_amdgcn_sbfe(w, 17, 5),
+            (float)(int)__builtin_amdgcn_sbfe(w, 22, 5),
+            (float)(int)__builtin_amdgcn_sbfe(w, 27, 5)};
+}
+
+// acc + sum_k c_k b_k, in this order wherever the codes come from.
+__device__ __forceinline__ float dct_accumulate(const DctCodes& c, const DctFactors& F, float acc)
+{
+    acc = __builtin_fmaf(c.c0, F.b0, acc);
+    acc = __builtin_fmaf(c.c1, F.b1, acc);
+    acc = __builtin_fmaf(c.c2, F.b2, acc);
+    acc = __builtin_fmaf(c.c3, F.b3, acc);
+    acc = __builtin_fmaf(c.c4, F.b4, acc);
+    return __builtin_fmaf(c.c5, F.b5, acc);
+}
+
+// c1(i), c2(i) for i = 0..7 in LDS, filled by the block's first eight
+// threads; the caller synchronises before the first read.
+__device__ __forceinline__ void dct_fill_cosines(float2* tab)
+{
+    if (threadIdx.x < 8) tab[threadIdx.x] = make_float2(dct_c1((int)threadIdx.x), dct_c2((int)threadIdx.x));
+}
+
+// Adds the tap at (clamped) texel coordinate x with weight w.
+__device__ __forceinline__ void dct_axis_add(DctAxis& a, const float2* tab, int x, float w)
+{
+    const float2 c = tab[x & 7];
+    a.s0 += w;
+    a.s1 = __builtin_fmaf(w, c.x, a.s1);
+    a.s2 = __builtin_fmaf(w, c.y, a.s2);
+}
+
+// The weight sums of NT <= 8 consecutive taps from x0, clamped to [0, hi], in
+// the (at most two) blocks they meet.
+struct DctAxisPair {
+    int blk0, blk1;
+    DctAxis a0, a1;
+};
+
+template <int NT>
+__device__ __forceinline__ DctAxisPair dct_axis_pair(const float2* tab, int x0, int hi, const float (&w)[4])
+{
+    auto clamped = [&](int x) { return x < 0 ? 0 : (x > hi ? hi : x); };
+    DctAxisPair r = {clamped(x0) >> 3, clamped(x0 + NT - 1) >> 3, {0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        const int x = clamped(x0 + k);
+        const bool second = (x >> 3) != r.blk0;
+        dct_axis_add(r.a0, tab, x, second ? 0.0f : w[k]);
+        dct_axis_add(r.a1, tab, x, second ? w[k] : 0.0f);
+    }
+    return r;
+}
+
 }  // namespace stf

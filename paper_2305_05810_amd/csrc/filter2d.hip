@@ -8,9 +8,10 @@
 // the negative weights (interp.h).
 //
 // Every kernel is generic over its texel source: stored texels of a format
-// (DenseSrc), or DCT-compressed blocks decoded one texel at a time
-// (DctSrc; the stochastic filters decode one texel per lookup instead of
-// 4 or 16, the case the paper makes for compressed formats).
+// (DenseSrc), or DCT-compressed blocks (DctSrc), of which the stochastic
+// filters decode one texel per lookup, the case the paper makes for
+// compressed formats.  The deterministic filters of DCT blocks have kernels
+// of their own, which weigh the blocks' coefficients and decode no texel.
 //
 // Raster position: x = uv.x * W - 0.5 (texel centres at half-integers of
 // uv * W); taps are clamped to the texture.
@@ -322,8 +323,8 @@ __global__ __launch_bounds__(BLOCK) void k_tex2d_deterministic(Src S, const floa
     cy += axis_weights_scaled<KIND>(ty, wy);
 #pragma unroll
     for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
-    // Wide sources (DCT blocks of 8+ channels) keep one row of taps in
-    // flight: unrolling all rows would hold every tap's words at once.
+    // Wide sources (materials, six channels) keep one row of taps in flight:
+    // unrolling all rows would hold every tap's texel at once.
     constexpr int ROWS_UNROLLED = CAP > 4 ? 1 : NT;
 #pragma unroll ROWS_UNROLLED
     for (int b = 0; b < NT; ++b) {
@@ -347,29 +348,6 @@ __global__ __launch_bounds__(BLOCK) void k_tex2d_deterministic(Src S, const floa
     block_store(S, out, n, live, oi, acc, order && scatter);
 }
 
-// Deterministic bicubic filtering of a Morton-sorted stream (neighbouring
-// queries close in the texture) of a source whose texels cost a decode.  The block decodes every texel of the bounding
-// box of its queries' clamped taps once into LDS and filters each query from
-// there; a block whose box exceeds STAGE_FLOATS values, or whose queries
-// would read fewer than STAGE_REUSE taps per decoded texel, decodes per tap
-// like k_tex2d_deterministic.  Both paths see the same decoded values and sum
-// them in the same order, so the results are the same.
-constexpr int STAGE_FLOATS = 8192;   // 32 KiB per block
-constexpr int STAGE_REUSE = 4;
-
-__device__ __forceinline__ int block_reduce_min(int v, int* red)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
-    __syncthreads();
-    int r = red[0];
-#pragma unroll
-    for (int k = 1; k < BLOCK / 64; ++k) r = min(r, red[k]);
-    __syncthreads();
-    return r;
-}
-
 // Discrete Gaussian weights of the 4x4 window i-1..i+2 (binary64, unnormalised).
 __device__ __forceinline__ void gauss_discrete_weights(double t, double inv2s2, double (&w)[4])
 {
@@ -380,27 +358,65 @@ __device__ __forceinline__ void gauss_discrete_weights(double t, double inv2s2, 
     }
 }
 
-// The discrete Gaussian mean (normalised 4x4 window) as a staged kind.
+// The discrete Gaussian mean (normalised 4x4 window) as a deterministic kind.
 constexpr int KIND_GAUSS_MEAN = 100;
 
-template <class Src, int KIND>
-__global__ __launch_bounds__(BLOCK) void k_tex2d_det_staged(Src S, const float* __restrict__ q, int32_t n,
-                                                            float* __restrict__ out, const int32_t* __restrict__ order,
-                                                            int scatter, unsigned long long* __restrict__ counters,
-                                                            float sigma)
+// Minimum over the wave of each lane's v, wave-uniform: data-parallel moves
+// within the rows of 16 lanes, then the four rows by scalar reads.
+__device__ __forceinline__ int wave_min(int v)
+{
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true));   // row_half_mirror
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true));   // row_mirror
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// Deterministic filtering of a DCT texture by blocks (dct_decode.h): the
+// window's weight sums per axis and block, then six multiply-adds per channel
+// and block the window meets, instead of decoding each of its 4 or 16 texels.
+//
+// With STAGE (the 16-tap kinds) the threads first decide together whether
+// their windows lie close enough to share blocks, as those of a frame in
+// pixel order or of a sorted stream do: at least STAGE_REUSE queries per block
+// of the bounding box of their taps, and the codes of its blocks fit the
+// tile.  Then the codes of the box's blocks are unpacked once into LDS (8
+// floats per channel: 6 codes, 16-byte reads); otherwise each query unpacks
+// the words of its own blocks.  Both ways see the same codes and accumulate
+// them in the same order, so the results are the same, bit for bit.
+//
+// Bound by VALU issue (weight sums and the multiply-adds; the streams alone
+// would take 75 us of the frame below).  4K frame of a 4096^2 set of 9
+// channels, 16 taps: 507 us with each texel of the taps' box decoded into
+// LDS once, 124 us so; 2M uniform uv: 228 us decoding every tap, 106 us so;
+// 4 taps, 4 channels, 2M pixels of a frame: 20.9 and 17.0 us.  An unguarded
+// group of four channels lets its LDS reads overlap (a test per channel: 141
+// us); tiles of 16, 20 and 32 KiB: 127, 124 and 147 us (the last one leaves 4
+// blocks per CU).
+constexpr int STAGE_FLOATS = 5120;   // 20 KiB per block: 8 blocks per CU
+// A staged block costs about as much as two queries unpacking it.
+constexpr int STAGE_REUSE = 2;
+
+template <int CAP, int KIND, bool STAGE>
+__global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* __restrict__ q, int32_t n,
+                                                   float* __restrict__ out, const int32_t* __restrict__ order,
+                                                   int scatter, unsigned long long* __restrict__ counters, float sigma)
 {
     constexpr int NT = KIND == KIND_LINEAR ? 2 : 4;
-    constexpr int CAP = Src::CAP;
-    static_assert(BLOCK * CAP <= STAGE_FLOATS, "the tile also stages the block's results");
-    __shared__ __align__(16) float tile[STAGE_FLOATS];
-    __shared__ int red[BLOCK / 64];
+        constexpr int TILE = STAGE ? STAGE_FLOATS : BLOCK * CAP;
+    static_assert(BLOCK * CAP <= TILE, "the tile also stages the block's results");
+    __shared__ __align__(16) float tile[TILE];
+    __shared__ float2 cosines[8];
+    __shared__ int box[5][BLOCK / 64];
+    dct_fill_cosines(cosines);
     const int32_t i0 = blockIdx.x * BLOCK + threadIdx.x;
     const bool live = i0 < n;
     const int32_t i = live ? i0 : 0;
     const int64_t oi = (order && scatter) ? (int64_t)order[i] : (int64_t)i;
-    float2 uv = reinterpret_cast<const float2*>(q)[i];
-    float x = uv.x * (float)S.w() - 0.5f;
-    float y = uv.y * (float)S.h() - 0.5f;
+    const float2 uv = reinterpret_cast<const float2*>(q)[i];
+    const float x = uv.x * (float)S.w() - 0.5f;
+    const float y = uv.y * (float)S.h() - 0.5f;
     int cx = 0, cy = 0;
     float tx = 0.0f, ty = 0.0f;
     const bool ok = cell_of(x, cx, tx) & cell_of(y, cy, ty);
@@ -424,78 +440,140 @@ __global__ __launch_bounds__(BLOCK) void k_tex2d_det_staged(Src S, const float* 
         cx += axis_weights_scaled<KIND>(tx, wx);
         cy += axis_weights_scaled<KIND>(ty, wy);
     }
-    // box of the clamped taps of the block's queries (clamping is monotone)
-    const bool in = live && ok;
     const int W1 = S.w() - 1, H1 = S.h() - 1;
-    const int x0 = block_reduce_min(in ? clampi(cx, W1) : INT_MAX, red);
-    const int x1 = -block_reduce_min(in ? -clampi(cx + NT - 1, W1) : INT_MAX, red);
-    const int y0 = block_reduce_min(in ? clampi(cy, H1) : INT_MAX, red);
-    const int y1 = -block_reduce_min(in ? -clampi(cy + NT - 1, H1) : INT_MAX, red);
-    const int nin = __syncthreads_count(in);
     const int C = S.channels();
-    const int ew = nin ? x1 - x0 + 1 : 0, eh = nin ? y1 - y0 + 1 : 0;   // both within the texture
-    const int64_t ntex = (int64_t)ew * eh;
+    // each channel's 6 codes take 8 floats; an odd multiple of 8 per block
+    // spreads the blocks a wave reads over the banks
+    const int bstride = (C | 1) * 8;
+    bool stage = false;
+    int bx0 = 0, by0 = 0, nbx = 0, nby = 0;   // the box's blocks
+    if constexpr (STAGE) {
+        // box of the clamped taps of the block's queries (clamping is monotone)
+        const bool in = live && ok;
+        const int m[4] = {wave_min(in ? clampi(cx, W1) : INT_MAX), wave_min(in ? -clampi(cx + NT - 1, W1) : INT_MAX),
+                          wave_min(in ? clampi(cy, H1) : INT_MAX), wave_min(in ? -clampi(cy + NT - 1, H1) : INT_MAX)};
+        const int cnt = __popcll(__ballot(in));
+        if (threadIdx.x % 64 == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) box[k][threadIdx.x / 64] = m[k];
+            box[4][threadIdx.x / 64] = cnt;
+        }
+    }
+    __syncthreads();
+    if constexpr (STAGE) {
+        // wave-uniform from here on
+        int r[4], nin = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int v = box[k][0];
+#pragma unroll
+            for (int w = 1; w < BLOCK / 64; ++w) v = min(v, box[k][w]);
+            r[k] = __builtin_amdgcn_readfirstlane(v);
+        }
+#pragma unroll
+        for (int w = 0; w < BLOCK / 64; ++w) nin += __builtin_amdgcn_readfirstlane(box[4][w]);
+        if (nin) {
+            bx0 = r[0] >> 3;
+            by0 = r[2] >> 3;
+            nbx = (-r[1] >> 3) - bx0 + 1;   // 1..8192 blocks per axis
+            nby = (-r[3] >> 3) - by0 + 1;
+        }
+        const int nb = nbx * nby;   // at most 2^26
+        // the same decision in every thread of the block
+        stage = nb && nb <= TILE / bstride && nb * STAGE_REUSE <= nin;
+        if (counters && threadIdx.x == 0) {   // {blocks that staged, blocks}, when counting is on
+            if (stage) atomicAdd(&counters[0], 1ull);
+            atomicAdd(&counters[1], 1ull);
+        }
+        if (stage) {
+            // a thread unpacks four channel words of a block
+            constexpr int G = CAP / 4;
+            const float inv_nbx = 1.0f / (float)nbx;
+            for (int t = threadIdx.x; t < nb * G; t += BLOCK) {
+                const int b = t / G, g = t - b * G;
+                const int yb = (int)(((float)b + 0.5f) * inv_nbx), xb = b - yb * nbx;   // b < 512: exact
+                const uint4 w4 = reinterpret_cast<const uint4*>(
+                    S.blocks + ((int64_t)(by0 + yb) * S.BW + bx0 + xb) * CAP)[g];
+                float* e = tile + b * bstride + g * 32;
+                const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (4 * g + j < C) {
+                        const DctCodes k = dct_codes(w[j]);
+                        *reinterpret_cast<float4*>(e + 8 * j) = make_float4(k.c0, k.c1, k.c2, k.c3);
+                        *reinterpret_cast<float2*>(e + 8 * j + 4) = make_float2(k.c4, k.c5);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+    const DctAxisPair px = dct_axis_pair<NT>(cosines, cx, W1, wx);
+    const DctAxisPair py = dct_axis_pair<NT>(cosines, cy, H1, wy);
+    // the kind's scale (36, 4 or 324 over both axes) divided out once per row of blocks
+    constexpr float inv = KIND == KIND_GAUSS_MEAN ? 1.0f : 1.0f / (axis_scale<KIND>() * axis_scale<KIND>());
     float acc[CAP];
 #pragma unroll
     for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
-    const bool stage = nin && ntex * C <= STAGE_FLOATS && ntex * STAGE_REUSE <= (int64_t)nin * NT * NT;
-    if (counters && threadIdx.x == 0) {   // {blocks that staged, blocks}, when counting is on
-        if (stage) atomicAdd(&counters[0], 1ull);
-        atomicAdd(&counters[1], 1ull);
-    }
-    if (stage) {
-        for (int t = threadIdx.x; t < (int)ntex; t += BLOCK) {
-            float v[CAP];
-            S.load(x0 + t % ew, y0 + t / ew, v);
+    const bool use = live && ok;
+    // the (at most) four blocks; a second block without taps has weight 0
+    const int nv = __any(use && py.blk1 != py.blk0) ? 2 : 1, nu = __any(use && px.blk1 != px.blk0) ? 2 : 1;
+#pragma unroll 1
+    for (int v = 0; v < nv; ++v) {
+        const DctRow row = dct_row({(v ? py.a1.s0 : py.a0.s0) * inv, (v ? py.a1.s1 : py.a0.s1) * inv,
+                                    (v ? py.a1.s2 : py.a0.s2) * inv});
+        const int by = v ? py.blk1 : py.blk0;
+#pragma unroll 1
+        for (int u = 0; u < nu; ++u) {
+            const DctFactors F = dct_factors(row, {u ? px.a1.s0 : px.a0.s0, u ? px.a1.s1 : px.a0.s1,
+                                                   u ? px.a1.s2 : px.a0.s2});
+            const int bx = u ? px.blk1 : px.blk0;
+            // whole groups of four channels without a test between them
+            if (stage) {   // (a query without a cell reads the first block)
+                const float* e = tile + (use ? ((by - by0) * nbx + (bx - bx0)) * bstride : 0);
+                auto one = [&](int c) {
+                    const float4 k0 = *reinterpret_cast<const float4*>(e + 8 * c);
+                    const float2 k1 = *reinterpret_cast<const float2*>(e + 8 * c + 4);
+                    acc[c] = dct_accumulate({k0.x, k0.y, k0.z, k0.w, k1.x, k1.y}, F, acc[c]);
+                };
 #pragma unroll
-            for (int c = 0; c < CAP; ++c)
-                if (c < C) tile[t * C + c] = v[c];
-        }
-        __syncthreads();
-        // tap offsets in the box (a query without a cell reads texel 0)
-        int ix[NT];
+                for (int g = 0; g < CAP; g += 4) {
+                    if (g + 4 <= C) {
+                        one(g);
+                        one(g + 1);
+                        one(g + 2);
+                        one(g + 3);
+                    } else {
+                        if (g < C) one(g);
+                        if (g + 1 < C) one(g + 1);
+                        if (g + 2 < C) one(g + 2);
+                    }
+                }
+            } else {
+                const uint4* b = reinterpret_cast<const uint4*>(S.blocks + ((int64_t)by * S.BW + bx) * CAP);
+                uint4 w4[CAP / 4];
 #pragma unroll
-        for (int a = 0; a < NT; ++a) ix[a] = in ? (clampi(cx + a, W1) - x0) * C : 0;
-        // wide sources keep one row of taps in registers at a time
-        constexpr int ROWS = CAP > 4 ? 1 : NT;
-#pragma unroll ROWS
-        for (int b = 0; b < NT; ++b) {
-            const int iy = in ? (clampi(cy + b, H1) - y0) * ew * C : 0;
-            float row[CAP];
+                for (int g = 0; g < CAP / 4; ++g) w4[g] = b[g];
+                auto one = [&](int c, uint32_t w) { acc[c] = dct_accumulate(dct_codes(w), F, acc[c]); };
 #pragma unroll
-            for (int c = 0; c < CAP; ++c) row[c] = 0.0f;
-#pragma unroll
-            for (int a = 0; a < NT; ++a) {
-                const float* e = tile + iy + ix[a];
-#pragma unroll
-                for (int c = 0; c < CAP; ++c) row[c] = __builtin_fmaf(wx[a], c < C ? e[c] : 0.0f, row[c]);
+                for (int g = 0; g < CAP / 4; ++g) {
+                    if (4 * g + 4 <= C) {
+                        one(4 * g, w4[g].x);
+                        one(4 * g + 1, w4[g].y);
+                        one(4 * g + 2, w4[g].z);
+                        one(4 * g + 3, w4[g].w);
+                    } else {
+                        if (4 * g < C) one(4 * g, w4[g].x);
+                        if (4 * g + 1 < C) one(4 * g + 1, w4[g].y);
+                        if (4 * g + 2 < C) one(4 * g + 2, w4[g].z);
+                    }
+                }
             }
-#pragma unroll
-            for (int c = 0; c < CAP; ++c) acc[c] = __builtin_fmaf(wy[b], row[c], acc[c]);
-        }
-    } else {
-        constexpr int ROWS_UNROLLED = CAP > 4 ? 1 : NT;
-#pragma unroll ROWS_UNROLLED
-        for (int b = 0; b < NT; ++b) {
-            int yy = clampi(cy + b, H1);
-            float row[CAP];
-#pragma unroll
-            for (int c = 0; c < CAP; ++c) row[c] = 0.0f;
-#pragma unroll
-            for (int a = 0; a < NT; ++a) {
-                float v[CAP];
-                S.load(clampi(cx + a, W1), yy, v);
-#pragma unroll
-                for (int c = 0; c < CAP; ++c) row[c] = __builtin_fmaf(wx[a], v[c], row[c]);
-            }
-#pragma unroll
-            for (int c = 0; c < CAP; ++c) acc[c] = __builtin_fmaf(wy[b], row[c], acc[c]);
         }
     }
-    constexpr float S2 = axis_scale<KIND>() * axis_scale<KIND>();
 #pragma unroll
-    for (int c = 0; c < CAP; ++c) acc[c] = !ok ? __builtin_nanf("") : (KIND == KIND_LINEAR ? acc[c] : acc[c] / S2);
-    __syncthreads();   // every thread is done with the tile: it now stages the results
+    for (int c = 0; c < CAP; ++c) acc[c] = ok ? acc[c] : __builtin_nanf("");
+    if constexpr (STAGE) __syncthreads();   // every thread is done with the tile: it now stages the results
     block_store_via(S, out, n, live, oi, acc, order && scatter, tile);
 }
 
@@ -777,6 +855,89 @@ __global__ __launch_bounds__(BLOCK) void k_tex2d_gauss(Src S, const float* __res
     }
 }
 
+// GAUSS_FIS_MEAN of a DCT texture by blocks (dct_decode.h): the (2R + 2)^2
+// taps meet at most ((2R + 8) / 8 + 1)^2 blocks, six multiply-adds per channel
+// each, instead of a decode per tap.  Each thread keeps the weight sums of its
+// columns per block in LDS (three values a block, one column per thread, rows
+// sized at launch) and takes its rows block by block, so that the lanes of a
+// wave read words together whatever their phase in a block.  Bound by the
+// binary64 erfc of each window edge; 2M pixels of a frame, 9 channels, sigma
+// 0.5 (100 taps): 1238 us with a decode per tap, 320 us so.
+template <int CAP>
+__global__ __launch_bounds__(BLOCK) void k_dct_gauss_mean(DctSrc<CAP> S, const float* __restrict__ q, int32_t n,
+                                                          float sigma, int32_t radius, float* __restrict__ out)
+{
+    extern __shared__ __align__(16) float sums[];
+    __shared__ float2 cosines[8];
+    dct_fill_cosines(cosines);
+    __syncthreads();
+    const int32_t i0 = blockIdx.x * BLOCK + threadIdx.x;
+    const bool live = i0 < n;
+    const float2 uv = reinterpret_cast<const float2*>(q)[live ? i0 : 0];
+    const float x = uv.x * (float)S.w() - 0.5f;
+    const float y = uv.y * (float)S.h() - 0.5f;
+    int cx = 0, cy = 0;
+    float tx = 0.0f, ty = 0.0f;
+    const bool ok = cell_of(x, cx, tx) & cell_of(y, cy, ty);
+    const int nt = live && ok ? 2 * radius + 2 : 0;   // no taps without a cell
+    const double sg = (double)sigma;
+    // weights of one axis in tap order: running differences of Phi
+    const int W1 = S.w() - 1, H1 = S.h() - 1, x0 = cx - radius, y0 = cy - radius;
+    const double xe = (double)x, ye = (double)y;
+    const int bx0 = clampi(x0, W1) >> 3;
+    int nbx = 0;
+    {
+        double p = gauss_phi(((double)x0 - xe - 0.5) / sg);
+        for (int k = 0; __any(k < nt);) {
+            DctAxis a = {0.0f, 0.0f, 0.0f};
+            for (int b = clampi(x0 + k, W1) >> 3; k < nt && clampi(x0 + k, W1) >> 3 == b; ++k) {
+                const double e = gauss_phi(((double)(x0 + k) - xe + 0.5) / sg);
+                dct_axis_add(a, cosines, clampi(x0 + k, W1), (float)(e - p));
+                p = e;
+            }
+            sums[(3 * nbx) * BLOCK + threadIdx.x] = a.s0;   // (a lane that is done writes zeros, at most
+            sums[(3 * nbx + 1) * BLOCK + threadIdx.x] = a.s1;   // as many rows as the widest lane)
+            sums[(3 * nbx + 2) * BLOCK + threadIdx.x] = a.s2;
+            ++nbx;
+        }
+    }
+    float acc[CAP];
+#pragma unroll
+    for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
+    const int C = S.channels(), BX1 = W1 >> 3;
+    double p = gauss_phi(((double)y0 - ye - 0.5) / sg);
+    for (int k = 0; __any(k < nt);) {
+        DctAxis a = {0.0f, 0.0f, 0.0f};
+        const int by = clampi(y0 + k, H1) >> 3;
+        for (; k < nt && clampi(y0 + k, H1) >> 3 == by; ++k) {
+            const double e = gauss_phi(((double)(y0 + k) - ye + 0.5) / sg);
+            dct_axis_add(a, cosines, clampi(y0 + k, H1), (float)(e - p));
+            p = e;
+        }
+        const DctRow row = dct_row(a);
+        for (int u = 0; u < nbx; ++u) {   // the same count in every lane of the wave
+            const float* e = sums + 3 * u * BLOCK + threadIdx.x;
+            const DctFactors F = dct_factors(row, {e[0], e[BLOCK], e[2 * BLOCK]});
+            const int bx = bx0 + u < BX1 ? bx0 + u : BX1;
+            const uint4* b = reinterpret_cast<const uint4*>(S.blocks + ((int64_t)by * S.BW + bx) * CAP);
+#pragma unroll
+            for (int g = 0; g < CAP / 4; ++g) {
+                if (4 * g < C) {   // (padding words of the last group add to unused channels)
+                    const uint4 w = b[g];
+                    acc[4 * g] = dct_accumulate(dct_codes(w.x), F, acc[4 * g]);
+                    acc[4 * g + 1] = dct_accumulate(dct_codes(w.y), F, acc[4 * g + 1]);
+                    acc[4 * g + 2] = dct_accumulate(dct_codes(w.z), F, acc[4 * g + 2]);
+                    acc[4 * g + 3] = dct_accumulate(dct_codes(w.w), F, acc[4 * g + 3]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CAP; ++c) acc[c] = ok ? acc[c] : __builtin_nanf("");
+    __syncthreads();   // the LDS rows now stage the results
+    block_store_via(S, out, n, live, (int64_t)i0, acc, false, sums);
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
@@ -797,16 +958,12 @@ void launch2d_kind(const Src& S, const float* q, int32_t n, int mode, uint32_t k
             hipLaunchKernelGGL((k_tex2d_stochastic<Src, KIND == KIND_BSPLINE, true>), grid, block, 0, stream, S, q, n,
                                key, out, idx, order, scatter);
     } else {
-        if constexpr (Src::DECODES && KIND != KIND_LINEAR) {
-            // a decoded source: neighbouring queries of a sorted stream or of
-            // a frame in pixel order share most of their 16 taps, so a block
-            // decodes its tap box once when the box is small enough (the
-            // kernel decides per block and otherwise decodes per tap)
-            hipLaunchKernelGGL((k_tex2d_det_staged<Src, KIND>), grid, block, 0, stream, S, q, n, out, order, scatter,
-                               stage_counters(), 0.0f);
-            return;
-        }
-        hipLaunchKernelGGL((k_tex2d_deterministic<Src, KIND>), grid, block, 0, stream, S, q, n, out, order, scatter);
+        if constexpr (Src::DECODES)   // by blocks; bilinear windows (2x2) share too little to stage
+            hipLaunchKernelGGL((k_dct_det<Src::CAP, KIND, KIND != KIND_LINEAR>), grid, block, 0, stream, S, q, n, out,
+                               order, scatter, KIND != KIND_LINEAR ? stage_counters() : nullptr, 0.0f);
+        else
+            hipLaunchKernelGGL((k_tex2d_deterministic<Src, KIND>), grid, block, 0, stream, S, q, n, out, order,
+                               scatter);
     }
 }
 
@@ -904,17 +1061,24 @@ hipError_t gauss2d_src(const Src& S, const float* q, int32_t n, float sigma, int
         break;
     case GAUSS_FIS_MEAN:
         if (2 * radius + 2 > GAUSS_MAX_TAPS) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_tex2d_gauss<Src, GAUSS_FIS_MEAN>), grid, block,
-                           (size_t)(2 * radius + 2) * BLOCK * sizeof(float), stream, S, q, n, sigma, radius, key,
-                           out, idx);
+        if constexpr (Src::DECODES) {
+            const size_t rows = 3 * (size_t)((2 * radius + 2 + 6) / 8 + 1);   // blocks the columns can meet
+            const size_t floats = rows > (size_t)Src::CAP ? rows : (size_t)Src::CAP;
+            hipLaunchKernelGGL((k_dct_gauss_mean<Src::CAP>), grid, block, floats * BLOCK * sizeof(float), stream, S, q,
+                               n, sigma, radius, out);
+        } else {
+            hipLaunchKernelGGL((k_tex2d_gauss<Src, GAUSS_FIS_MEAN>), grid, block,
+                               (size_t)(2 * radius + 2) * BLOCK * sizeof(float), stream, S, q, n, sigma, radius, key,
+                               out, idx);
+        }
         break;
     case GAUSS_DISCRETE:
         hipLaunchKernelGGL((k_tex2d_gauss<Src, GAUSS_DISCRETE>), grid, block, 0, stream, S, q, n, sigma, radius, key,
                            out, idx);
         break;
     case GAUSS_DISCRETE_MEAN:
-        if constexpr (Src::DECODES)   // decoded sources: each block decodes its taps' box once (when it pays)
-            hipLaunchKernelGGL((k_tex2d_det_staged<Src, KIND_GAUSS_MEAN>), grid, block, 0, stream, S, q, n, out,
+        if constexpr (Src::DECODES)
+            hipLaunchKernelGGL((k_dct_det<Src::CAP, KIND_GAUSS_MEAN, true>), grid, block, 0, stream, S, q, n, out,
                                nullptr, 0, stage_counters(), sigma);
         else
             hipLaunchKernelGGL((k_tex2d_gauss<Src, GAUSS_DISCRETE_MEAN>), grid, block, 0, stream, S, q, n, sigma,
