@@ -14,9 +14,9 @@
 // Training (binary32): per step a batch of texel positions, forward and
 // backward through the MLP and the bilinear interpolation, mean squared
 // error against the target texels, Adam.  One kernel processes tiles of 32
-// samples with the weights in LDS and accumulates weight gradients per block;
-// a second kernel reduces the blocks in a fixed order; latent gradients are
-// scattered with atomics.
+// samples on the binary32 matrix cores and sums weight gradients per block; a
+// second one sums the blocks in a fixed order and makes the Adam steps; latent
+// gradients are scattered with atomics.
 //
 // Inference: latents rounded to binary16, weights to bfloat16, biases kept in
 // binary32.  Each wave decodes 32 texels per MFMA batch with
@@ -43,13 +43,9 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NL, OFF_W2 = OFF_B1 + NH, OFF_B
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NO * NH, NPARAM = OFF_B3 + NO;
 constexpr int PSTRIDE = NPARAM + 1;   // per-block partial gradients + loss
 constexpr int TS = 32;                 // samples per training tile
-constexpr int TBLOCK = 256;
-// Weight-gradient ownership (each in registers across all tiles of a
-// block): thread t holds the W2 entries of rows 16 (t / 64) + r (r < 16),
-// column t % 64; threads 0..63 also hold row t of W1 and b1[t], threads
-// 64..127 column t - 64 of W3 and b2[t - 64], threads 128..135 b3[t - 128].
-constexpr int OWN2 = NH * NH / TBLOCK;                        // 16
-static_assert(NL == 8 && NO == 8 && NH == 64 && TBLOCK == 256, "the ownership above");
+constexpr int TBLOCK = 512;
+constexpr int TRAIN_BLOCKS = 512;      // one resident set: two blocks per CU
+static_assert(NL == 8 && NO == 8 && NH == 64, "the training kernel's operand layouts");
 
 struct TrainArgs {
     const float* lat;
@@ -69,319 +65,419 @@ __device__ __forceinline__ int clampi(int v, int hi)
     return v < 0 ? 0 : (v > hi ? hi : v);
 }
 
-__global__ __launch_bounds__(TBLOCK) void k_ntex_train(TrainArgs a)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Row 4g + r of a 16-row operand block holds unit 4r + g of the block: the
+// accumulator registers r of the lanes (g, n) are then the k-steps of the next
+// product in unit order (step r, k-slot g: unit 4r + g).
+__host__ __device__ constexpr int unit_of_row(int row)
 {
-    // Operands of the products are read four values at a time (16-byte LDS
-    // reads), each read serving several FMAs; every sum keeps its order.
-    // Rows of NH + 4 floats stay 16-byte aligned and spread the 16 lanes of a
-    // read phase over all banks.  80 KiB per block: two blocks per CU.
-    constexpr int R4 = NH + 4;
-    __shared__ __align__(16) float sW2[NH][R4], sW2T[NH][R4], sW3[NO][R4], sW1T[NL][R4];
-    __shared__ __align__(16) float sH1[TS][R4], sH2[TS][R4], sD2[TS][R4], sD1[TS][R4];
-    __shared__ __align__(16) float sZ[TS][NL], sDY[TS][NO];
-    __shared__ float sB1[NH], sB2[NH], sB3[NO], sT[TS][NO + 1];
-    __shared__ int32_t sCI[TS][4];
-    __shared__ float sCW[TS][4];
-    __shared__ int32_t sTex[TS];
-    static_assert(TS * (NO + 1) >= TBLOCK, "the loss reduction reuses sT");
-    const int t = threadIdx.x;
-    for (int p = t; p < NPARAM; p += TBLOCK) {
-        float v = a.mlp[p];
-        if (p < OFF_B1) sW1T[p % NL][p / NL] = v;
-        else if (p < OFF_W2) sB1[p - OFF_B1] = v;
-        else if (p < OFF_B2) {
-            sW2[(p - OFF_W2) / NH][(p - OFF_W2) % NH] = v;
-            sW2T[(p - OFF_W2) % NH][(p - OFF_W2) / NH] = v;
-        }
-        else if (p < OFF_W3) sB2[p - OFF_B2] = v;
-        else if (p < OFF_B3) sW3[(p - OFF_W3) / NH][(p - OFF_W3) % NH] = v;
-        else sB3[p - OFF_B3] = v;
-    }
-    // gradients owned by this thread (see the ownership note above)
-    float acc2[OWN2], accw[NL], accb = 0.0f;
-#pragma unroll
-    for (int r = 0; r < OWN2; ++r) acc2[r] = 0.0f;
-#pragma unroll
-    for (int r = 0; r < NL; ++r) accw[r] = 0.0f;
-    float lacc = 0.0f;
-    const int s = t / 8, k = t % 8;       // (sample, channel) for the gather/scatter and output phases
-    const int ha = t % NH, hs = t / NH;   // (hidden unit, first sample) for the 32 x 64 phases
-    for (int tile = blockIdx.x; tile * TS < a.B; tile += gridDim.x) {
-        const int gs = tile * TS + s;
-        const bool live = gs < a.B;
-        __syncthreads();   // previous tile's LDS reads are done
-        if (k == 0) {
-            int i = 0, j = 0;
-            if (live) {
-                if (a.pos) {   // caller-supplied positions are clamped into the texture
-                    i = clampi(a.pos[2 * (int64_t)gs], a.W - 1);
-                    j = clampi(a.pos[2 * (int64_t)gs + 1], a.H - 1);
-                } else {
-                    uint32_t h = pcg(a.kstep ^ (uint32_t)gs);
-                    i = (int)(h % (uint32_t)a.W);
-                    j = (int)(pcg(h + 1u) % (uint32_t)a.H);
-                }
-            }
-            float X = ((float)i + 0.5f) * a.rx - 0.5f, Y = ((float)j + 0.5f) * a.ry - 0.5f;
-            float fx0 = floorf(X), fy0 = floorf(Y);
-            float fx = X - fx0, fy = Y - fy0;
-            int x0 = (int)fx0, y0 = (int)fy0;
-            int xa = clampi(x0, a.LW - 1), xb = clampi(x0 + 1, a.LW - 1);
-            int ya = clampi(y0, a.LH - 1), yb = clampi(y0 + 1, a.LH - 1);
-            sCI[s][0] = ya * a.LW + xa;
-            sCI[s][1] = ya * a.LW + xb;
-            sCI[s][2] = yb * a.LW + xa;
-            sCI[s][3] = yb * a.LW + xb;
-            sCW[s][0] = (1.0f - fx) * (1.0f - fy);
-            sCW[s][1] = fx * (1.0f - fy);
-            sCW[s][2] = (1.0f - fx) * fy;
-            sCW[s][3] = fx * fy;
-            sTex[s] = j * a.W + i;
-        }
-        __syncthreads();
-        {
-            float z = 0.0f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) z = __builtin_fmaf(sCW[s][c], a.lat[(int64_t)sCI[s][c] * NL + k], z);
-            sZ[s][k] = live ? z : 0.0f;
-            sT[s][k] = live ? a.target[(int64_t)sTex[s] * NO + k] : 0.0f;
-        }
-        __syncthreads();
-        {   // H1 = relu(W1 Z + b1): the thread's W1 row once, two reads per sample
-            float w[NL];
-#pragma unroll
-            for (int kk = 0; kk < NL; ++kk) w[kk] = sW1T[kk][ha];
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) {
-                const int s2 = hs + 4 * r;
-                const float4 z0 = *reinterpret_cast<const float4*>(&sZ[s2][0]);
-                const float4 z1 = *reinterpret_cast<const float4*>(&sZ[s2][4]);
-                float v = sB1[ha];
-                v = __builtin_fmaf(w[0], z0.x, v);
-                v = __builtin_fmaf(w[1], z0.y, v);
-                v = __builtin_fmaf(w[2], z0.z, v);
-                v = __builtin_fmaf(w[3], z0.w, v);
-                v = __builtin_fmaf(w[4], z1.x, v);
-                v = __builtin_fmaf(w[5], z1.y, v);
-                v = __builtin_fmaf(w[6], z1.z, v);
-                v = __builtin_fmaf(w[7], z1.w, v);
-                sH1[s2][ha] = fmaxf(v, 0.0f);
-            }
-        }
-        __syncthreads();
-        {   // H2 = relu(W2 H1 + b2): each W2 row read serves the thread's 8 samples
-            float v[TS / 4];
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) v[r] = sB2[ha];
-#pragma unroll 4
-            for (int b = 0; b < NH; b += 4) {
-                const float4 w = *reinterpret_cast<const float4*>(&sW2[ha][b]);
-#pragma unroll
-                for (int r = 0; r < TS / 4; ++r) {
-                    const float4 x = *reinterpret_cast<const float4*>(&sH1[hs + 4 * r][b]);
-                    v[r] = __builtin_fmaf(w.x, x.x, v[r]);
-                    v[r] = __builtin_fmaf(w.y, x.y, v[r]);
-                    v[r] = __builtin_fmaf(w.z, x.z, v[r]);
-                    v[r] = __builtin_fmaf(w.w, x.w, v[r]);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) sH2[hs + 4 * r][ha] = fmaxf(v[r], 0.0f);
-        }
-        __syncthreads();
-        {   // Y = W3 H2 + b3 and the loss: thread (s, k)
-            float y = sB3[k];
-#pragma unroll 4
-            for (int b = 0; b < NH; b += 4) {
-                const float4 w = *reinterpret_cast<const float4*>(&sW3[k][b]);
-                const float4 x = *reinterpret_cast<const float4*>(&sH2[s][b]);
-                y = __builtin_fmaf(w.x, x.x, y);
-                y = __builtin_fmaf(w.y, x.y, y);
-                y = __builtin_fmaf(w.z, x.z, y);
-                y = __builtin_fmaf(w.w, x.w, y);
-            }
-            float e = y - sT[s][k];
-            if (live) lacc = __builtin_fmaf(e, e, lacc);
-            sDY[s][k] = live ? e * a.dscale : 0.0f;
-        }
-        __syncthreads();
-        {   // D2 = (W3^T dY) * [H2 > 0]: the thread's W3 column once
-            float w[NO];
-#pragma unroll
-            for (int c = 0; c < NO; ++c) w[c] = sW3[c][ha];
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) {
-                const int s2 = hs + 4 * r;
-                const float4 d0 = *reinterpret_cast<const float4*>(&sDY[s2][0]);
-                const float4 d1 = *reinterpret_cast<const float4*>(&sDY[s2][4]);
-                float v = 0.0f;
-                v = __builtin_fmaf(w[0], d0.x, v);
-                v = __builtin_fmaf(w[1], d0.y, v);
-                v = __builtin_fmaf(w[2], d0.z, v);
-                v = __builtin_fmaf(w[3], d0.w, v);
-                v = __builtin_fmaf(w[4], d1.x, v);
-                v = __builtin_fmaf(w[5], d1.y, v);
-                v = __builtin_fmaf(w[6], d1.z, v);
-                v = __builtin_fmaf(w[7], d1.w, v);
-                sD2[s2][ha] = sH2[s2][ha] > 0.0f ? v : 0.0f;
-            }
-        }
-        __syncthreads();
-        {   // D1 = (W2^T D2) * [H1 > 0]
-            float v[TS / 4];
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) v[r] = 0.0f;
-#pragma unroll 4
-            for (int b = 0; b < NH; b += 4) {
-                const float4 w = *reinterpret_cast<const float4*>(&sW2T[ha][b]);   // W2[b..b+3][ha]
-#pragma unroll
-                for (int r = 0; r < TS / 4; ++r) {
-                    const float4 d = *reinterpret_cast<const float4*>(&sD2[hs + 4 * r][b]);
-                    v[r] = __builtin_fmaf(w.x, d.x, v[r]);
-                    v[r] = __builtin_fmaf(w.y, d.y, v[r]);
-                    v[r] = __builtin_fmaf(w.z, d.z, v[r]);
-                    v[r] = __builtin_fmaf(w.w, d.w, v[r]);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < TS / 4; ++r) sD1[hs + 4 * r][ha] = sH1[hs + 4 * r][ha] > 0.0f ? v[r] : 0.0f;
-        }
-        __syncthreads();
-        {   // dZ = W1^T D1, scattered to the four latent corners
-            float dz = 0.0f;
-#pragma unroll 4
-            for (int b = 0; b < NH; b += 4) {
-                const float4 w = *reinterpret_cast<const float4*>(&sW1T[k][b]);   // W1[b..b+3][k]
-                const float4 d = *reinterpret_cast<const float4*>(&sD1[s][b]);
-                dz = __builtin_fmaf(w.x, d.x, dz);
-                dz = __builtin_fmaf(w.y, d.y, dz);
-                dz = __builtin_fmaf(w.z, d.z, dz);
-                dz = __builtin_fmaf(w.w, d.w, dz);
-            }
-            if (live) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) atomicAdd(a.g_lat + (int64_t)sCI[s][c] * NL + k, sCW[s][c] * dz);
-            }
-        }
-        {   // dW2[ua][ub] = sum_q D2[q][ua] H1[q][ub], ua = 16 (t/64) + r, ub = t%64:
-            // per sample one H1 value and four 16-byte reads of D2
-            float g[OWN2];
-#pragma unroll
-            for (int r = 0; r < OWN2; ++r) g[r] = 0.0f;
-            const int u0 = OWN2 * (t / NH), ub = t % NH;
-#pragma unroll 4
-            for (int q = 0; q < TS; ++q) {
-                const float h = sH1[q][ub];
-#pragma unroll
-                for (int r4 = 0; r4 < OWN2; r4 += 4) {
-                    const float4 d = *reinterpret_cast<const float4*>(&sD2[q][u0 + r4]);
-                    g[r4] = __builtin_fmaf(d.x, h, g[r4]);
-                    g[r4 + 1] = __builtin_fmaf(d.y, h, g[r4 + 1]);
-                    g[r4 + 2] = __builtin_fmaf(d.z, h, g[r4 + 2]);
-                    g[r4 + 3] = __builtin_fmaf(d.w, h, g[r4 + 3]);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < OWN2; ++r) acc2[r] += g[r];
-        }
-        if (t < 2 * NH) {   // dW1 row t and b1[t] / dW3 column t - 64 and b2[t - 64]
-            const int ua = t % NH;
-            const bool first = t < NH;
-            const float(*D)[R4] = first ? sD1 : sD2;
-            const float(*X)[NL] = first ? sZ : sDY;
-            const float(*Hq)[R4] = first ? sD1 : sH2;
-            float g[NL], gb = 0.0f;
-#pragma unroll
-            for (int r = 0; r < NL; ++r) g[r] = 0.0f;
-#pragma unroll 4
-            for (int q = 0; q < TS; ++q) {
-                const float hq = Hq[q][ua];   // D1[q][ua] (dW1) or H2[q][ua] (dW3)
-                const float4 x0 = *reinterpret_cast<const float4*>(&X[q][0]);   // Z[q][.] or dY[q][.]
-                const float4 x1 = *reinterpret_cast<const float4*>(&X[q][4]);
-                g[0] = __builtin_fmaf(first ? hq : x0.x, first ? x0.x : hq, g[0]);
-                g[1] = __builtin_fmaf(first ? hq : x0.y, first ? x0.y : hq, g[1]);
-                g[2] = __builtin_fmaf(first ? hq : x0.z, first ? x0.z : hq, g[2]);
-                g[3] = __builtin_fmaf(first ? hq : x0.w, first ? x0.w : hq, g[3]);
-                g[4] = __builtin_fmaf(first ? hq : x1.x, first ? x1.x : hq, g[4]);
-                g[5] = __builtin_fmaf(first ? hq : x1.y, first ? x1.y : hq, g[5]);
-                g[6] = __builtin_fmaf(first ? hq : x1.z, first ? x1.z : hq, g[6]);
-                g[7] = __builtin_fmaf(first ? hq : x1.w, first ? x1.w : hq, g[7]);
-                gb += D[q][ua];   // b1 from D1, b2 from D2
-            }
-#pragma unroll
-            for (int r = 0; r < NL; ++r) accw[r] += g[r];
-            accb += gb;
-        } else if (t < 2 * NH + NO) {   // b3
-            float gb = 0.0f;
-            for (int q = 0; q < TS; ++q) gb += sDY[q][t - 2 * NH];
-            accb += gb;
+    return 4 * (row % 4) + row / 4;
+}
+
+// Where the row of sample s begins in a [32][64] matrix in LDS: 16 (s % 4) +
+// 4 (s / 4 % 4) banks on, so that the 16-byte accesses of 16 samples at one
+// column and the 4-byte accesses of 16 columns of 4 successive samples both
+// meet every bank once.
+__host__ __device__ constexpr int train_row(int s)
+{
+    return s / 16 * 1280 + s / 4 % 4 * 324 + s % 4 * 80;
+}
+constexpr int TMAT = train_row(TS);
+
+constexpr int ZSTRIDE = 16;
+struct TrainShared {
+    // [sample][row of the unit] (train_row); D1 takes the place of H2
+    float h1[TMAT], h2d1[TMAT], d2[TMAT];
+    float z[2][TS * ZSTRIDE];   // [sample][2g + t: channel 4t + g]; column 8 is 1, 9..15 are 0
+    float y[TS * ZSTRIDE];      // the output's gradient, later the latents', columns as in z; 8..15 are 0
+    float t[TS * NO];           // target, columns as in z; at the end the loss of either half
+    float b1[NH], b2[NH], b3[16];   // biases by row
+    f32x4 w2[16][64], w2t[16][64], w3[4][64], w1t[4][64];   // A operand images: [4 mb + kb or kb][lane], k-steps r
+};
+static_assert(sizeof(TrainShared) <= 80 * 1024, "two blocks per CU");
+
+// What thread (sample s, channel k) of a tile reads from memory: the first 256
+// threads the latent corners, the others the target.
+struct TrainGather {
+    float v0, v1, v2, v3;
+    float w0, w1, w2, w3;
+    uint32_t o0, o1, o2, o3;   // byte offsets of the corners' channel (a latent grid is below 4 GiB)
+    bool live;
+};
+
+__device__ __forceinline__ TrainGather train_gather(const TrainArgs& a, int32_t tile, int s, int k, bool latents)
+{
+    TrainGather r = {};
+    const int64_t gs = (int64_t)tile * TS + s;
+    r.live = gs < a.B;
+    int i = 0, j = 0;
+    if (r.live) {
+        // h mod size without a division where the size is a power of two
+        auto mod = [](uint32_t h, uint32_t size) { return (int)((size & (size - 1)) ? h % size : h & (size - 1)); };
+        if (a.pos) {   // caller-supplied positions are clamped into the texture
+            i = clampi(a.pos[2 * gs], a.W - 1);
+            j = clampi(a.pos[2 * gs + 1], a.H - 1);
+        } else {
+            const uint32_t h = pcg(a.kstep ^ (uint32_t)gs);
+            i = mod(h, (uint32_t)a.W);
+            j = mod(pcg(h + 1u), (uint32_t)a.H);
         }
     }
-    float* out = a.partial + (int64_t)blockIdx.x * PSTRIDE;
+    if (!latents) {
+        r.v0 = a.target[((int64_t)j * a.W + i) * NO + k];
+        return r;
+    }
+    const float X = ((float)i + 0.5f) * a.rx - 0.5f, Y = ((float)j + 0.5f) * a.ry - 0.5f;
+    const float fx0 = floorf(X), fy0 = floorf(Y);
+    const float fx = X - fx0, fy = Y - fy0;
+    const int x0 = (int)fx0, y0 = (int)fy0;
+    const int xa = clampi(x0, a.LW - 1), xb = clampi(x0 + 1, a.LW - 1);
+    const int ya = clampi(y0, a.LH - 1), yb = clampi(y0 + 1, a.LH - 1);
+    auto corner = [&](int x, int y) { return (uint32_t)(y * a.LW + x) * (NL * 4u) + 4u * (uint32_t)k; };
+    r.o0 = corner(xa, ya);
+    r.o1 = corner(xb, ya);
+    r.o2 = corner(xa, yb);
+    r.o3 = corner(xb, yb);
+    r.w0 = (1.0f - fx) * (1.0f - fy);
+    r.w1 = fx * (1.0f - fy);
+    r.w2 = (1.0f - fx) * fy;
+    r.w3 = fx * fy;
+    auto load = [&](uint32_t o) {
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.lat) + (size_t)o);
+    };
+    r.v0 = load(r.o0);
+    r.v1 = load(r.o1);
+    r.v2 = load(r.o2);
+    r.v3 = load(r.o3);
+    return r;
+}
+
+// Adds a tile's latent gradient (sample s, channel k) to the four corners.
+__device__ __forceinline__ void train_scatter(const TrainArgs& a, const TrainGather& r, float dz)
+{
+    if (!r.live) return;
+    auto add = [&](uint32_t o, float v) {
+        atomicAdd(reinterpret_cast<float*>(reinterpret_cast<char*>(a.g_lat) + (size_t)o), v);
+    };
+    add(r.o0, r.w0 * dz);
+    add(r.o1, r.w1 * dz);
+    add(r.o2, r.w2 * dz);
+    add(r.o3, r.w3 * dz);
+}
+
+// A chain of 16 matrix instructions: acc + A B over 64 k-slots, A from an
+// operand image, B from the lane's sample's row in LDS (from its column 4g).
+// Two blocks of operands in flight, held back by the scheduling barriers.
+__device__ __forceinline__ f32x4 train_chain(const f32x4 (*A)[64], const float* B, int lane, f32x4 acc)
+{
+    f32x4 w[2], x[2];
+    w[0] = A[0][lane];
+    x[0] = *reinterpret_cast<const f32x4*>(B);
 #pragma unroll
-    for (int r = 0; r < OWN2; ++r) out[OFF_W2 + (OWN2 * (t / NH) + r) * NH + t % NH] = acc2[r];
+    for (int kb = 0; kb < 4; ++kb) {
+        if (kb < 3) {
+            w[(kb + 1) % 2] = A[kb + 1][lane];
+            x[(kb + 1) % 2] = *reinterpret_cast<const f32x4*>(B + 16 * (kb + 1));
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[kb % 2][r], x[kb % 2][r], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc;
+}
+
+__device__ __forceinline__ f32x4 relu4(f32x4 v)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+    return v;
+}
+
+__device__ __forceinline__ f32x4 mask4(f32x4 v, const f32x4& h)   // v where h > 0
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = h[r] > 0.0f ? v[r] : 0.0f;
+    return v;
+}
+
+// Forward and backward pass over tiles of 32 samples, eight waves per tile,
+// every product on the binary32 matrix cores (v_mfma_f32_16x16x4_f32): wave
+// (mb, nh) makes units 16 mb .. 16 mb + 15 of samples 16 nh .. 16 nh + 15 of
+// each layer, and its share of the weight gradients.
+//
+// Activations are products [unit][sample]: lane (g, n) = (lane / 16, lane % 16)
+// holds four units of sample 16 nh + n.  The waves exchange them through LDS,
+// where a lane reads its sample's row as the next product's B operand; rows are
+// numbered (unit_of_row) so that the k-slots of successive steps run through
+// the units in order.  A matrix instruction adds its four products one after
+// the other, each rounded once like an FMA, so every activation and every
+// gradient has the bits of the plain FMA loops over units and samples.  The 8
+// channels of the latents and of the output occupy rows 4g + {0, 1} (channels
+// g and 4 + g).  A weight gradient sums over samples: its operands are read
+// from the same LDS matrices with the sample in the k-slot, 4 bytes a lane,
+// and each tile's sum, formed from zero, is added to the wave's registers.
+//
+// 608 matrix instructions of 32 cycles per tile would take 65 us for 262,144
+// samples on 1,024 SIMDs; the chain of seven barriers per tile, each with an
+// LDS round trip and a dependent chain, holds the pass at 129 us (matrix cores
+// busy 50% of the cycles; without the atomics 127 us, without the gathers 122
+// us).  Four waves per SIMD from two blocks per CU fill each other's gaps, and
+// a tile's gathers are issued a tile ahead.  The same products as register-
+// blocked FMAs from LDS took 220 us.
+__global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
+{
+    __shared__ __align__(16) char smem[sizeof(TrainShared)];
+    TrainShared& S = *reinterpret_cast<TrainShared*>(smem);
+    const int t = threadIdx.x, lane = t % 64, wave = t / 64, n = lane % 16, g = lane / 16;
+    const int mb = wave % 4, nh = wave / 4;
+    {   // Operand images: every weight is loaded once and put where its images
+        // hold it -- lane l of an A operand holds row l % 16, k-slot l / 16.
+        float* w2 = reinterpret_cast<float*>(S.w2);
+        float* w2t = reinterpret_cast<float*>(S.w2t);
+        float* w3 = reinterpret_cast<float*>(S.w3);
+        float* w1t = reinterpret_cast<float*>(S.w1t);
+        constexpr int PER = NH * NH / TBLOCK;   // 8 entries of a W2 row
+        const f32x4 wa = *reinterpret_cast<const f32x4*>(a.mlp + OFF_W2 + PER * t),
+                    wb = *reinterpret_cast<const f32x4*>(a.mlp + OFF_W2 + PER * t + 4);
+        const float v1 = a.mlp[OFF_W1 + t], v3 = a.mlp[OFF_W3 + t];   // 512 of each
+        auto place = [](int row, int k) { return (k / 16 * 64 + k % 4 * 16 + row) * 4 + k % 16 / 4; };
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const float v = e < 4 ? wa[e % 4] : wb[e % 4];
+            const int m = PER * t / NH, k = PER * t % NH + e;
+            w2[m / 16 * 1024 + place(unit_of_row(m % 16), k)] = v;
+            w2t[k / 16 * 1024 + place(unit_of_row(k % 16), m)] = v;
+        }
+        w3[place(unit_of_row(t / NH), t % NH)] = v3;    // channel c in row unit_of_row(c), a row of two in four
+        w1t[place(unit_of_row(t % NL), t / NL)] = v1;
+        for (int e = t; e < 4 * 64 * 4; e += TBLOCK)
+            if (e / 4 % 4 >= 2) w3[e] = w1t[e] = 0.0f;   // rows 4g + {2, 3} are padding
+        for (int e = t; e < TS * (ZSTRIDE - 8); e += TBLOCK) {
+            const int at = e / (ZSTRIDE - 8) * ZSTRIDE + 8 + e % (ZSTRIDE - 8);
+            S.z[0][at] = S.z[1][at] = e % (ZSTRIDE - 8) == 0 ? 1.0f : 0.0f;
+            S.y[at] = 0.0f;
+        }
+    }
+    // this wave's smaller operands, in registers
+    float w1[2], w3t[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int u = 16 * mb + unit_of_row(n), c = 4 * r + g;
+        w1[r] = a.mlp[OFF_W1 + u * NL + c];
+        w3t[r] = a.mlp[OFF_W3 + c * NH + u];
+    }
     if (t < NH) {
-#pragma unroll
-        for (int r = 0; r < NL; ++r) out[OFF_W1 + t * NL + r] = accw[r];
-        out[OFF_B1 + t] = accb;
-    } else if (t < 2 * NH) {
-#pragma unroll
-        for (int r = 0; r < NO; ++r) out[OFF_W3 + r * NH + (t - NH)] = accw[r];
-        out[OFF_B2 + t - NH] = accb;
-    } else if (t < 2 * NH + NO) {
-        out[OFF_B3 + t - 2 * NH] = accb;
+        S.b1[t] = a.mlp[OFF_B1 + t / 16 * 16 + unit_of_row(t % 16)];
+        S.b2[t] = a.mlp[OFF_B2 + t / 16 * 16 + unit_of_row(t % 16)];
     }
-    float* sRed = &sT[0][0];
-    __syncthreads();   // the last tile's reads of sT are done
-    sRed[t] = lacc;
-    __syncthreads();
-    for (int st = TBLOCK / 2; st > 0; st >>= 1) {
-        if (t < st) sRed[t] += sRed[t + st];
+    if (t < 16) S.b3[t] = t % 4 < 2 ? a.mlp[OFF_B3 + unit_of_row(t)] : 0.0f;
+    // LDS places: column 4g of the lane's sample (16-byte accesses), column n
+    // of sample g, whose successors 4 j + g are constants further on (4-byte
+    // accesses of the weight gradients)
+    const int smp = 16 * nh + n, row0 = train_row(smp) + 4 * g, col0 = train_row(g) + n;
+    // gradients over the block's tiles: dW2 rows of block mb, columns of
+    // blocks 2 nh and 2 nh + 1; dW1 and db1 (nh = 0: column 8) or db2 (nh = 1:
+    // column 8); dW3 of unit block 2 (mb - 2) + nh (mb >= 2); db3
+    f32x4 g20 = (f32x4)0.0f, g21 = g20, g1 = g20, g3 = g20, gb3 = g20;
+    float lacc = 0.0f;
+    const int s8 = t % 256 / 8, k8 = t % 8, c8 = 2 * (k8 % 4) + k8 / 4;
+    const bool latents = t < 256;
+    const int32_t ntiles = (a.B - 1) / TS + 1;
+    TrainGather cur = train_gather(a, blockIdx.x, s8, k8, latents), prev = {};
+    int buf = 0;
+    for (int32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (latents) {
+            float z = 0.0f;
+            z = __builtin_fmaf(cur.w0, cur.v0, z);
+            z = __builtin_fmaf(cur.w1, cur.v1, z);
+            z = __builtin_fmaf(cur.w2, cur.v2, z);
+            z = __builtin_fmaf(cur.w3, cur.v3, z);
+            S.z[buf][s8 * ZSTRIDE + c8] = cur.live ? z : 0.0f;
+        } else {
+            S.t[s8 * NO + c8] = cur.v0;
+        }
+        __syncthreads();   // z, t; the previous tile is done with the matrices
+        if (latents) train_scatter(a, prev, S.y[s8 * ZSTRIDE + c8]);
+        prev = cur;
+        const int64_t next = (int64_t)tile + gridDim.x;
+        cur = train_gather(a, next < ntiles ? (int32_t)next : tile, s8, k8, latents);
+        const bool live = (int64_t)tile * TS + smp < a.B;
+        // H1 = relu(W1 Z + b1)
+        const float2 z = *reinterpret_cast<const float2*>(&S.z[buf][smp * ZSTRIDE + 2 * g]);
+        const int own = row0 + 16 * mb;
+        f32x4 h1 = *reinterpret_cast<const f32x4*>(&S.b1[16 * mb + 4 * g]);
+        h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[0], z.x, h1, 0, 0, 0);
+        h1 = relu4(__builtin_amdgcn_mfma_f32_16x16x4f32(w1[1], z.y, h1, 0, 0, 0));
+        *reinterpret_cast<f32x4*>(&S.h1[own]) = h1;
         __syncthreads();
+        // H2 = relu(W2 H1 + b2)
+        f32x4 h2 = *reinterpret_cast<const f32x4*>(&S.b2[16 * mb + 4 * g]);
+        h2 = relu4(train_chain(&S.w2[4 * mb], S.h1 + row0, lane, h2));
+        *reinterpret_cast<f32x4*>(&S.h2d1[own]) = h2;
+        __syncthreads();
+        if (mb == 0) {   // Y = W3 H2 + b3, the loss and its gradient
+            const f32x4 y = train_chain(S.w3, S.h2d1 + row0, lane, *reinterpret_cast<const f32x4*>(&S.b3[4 * g]));
+            const float2 target = *reinterpret_cast<const float2*>(&S.t[smp * NO + 2 * g]);
+            const float e0 = y[0] - target.x, e1 = y[1] - target.y;
+            if (live) lacc = __builtin_fmaf(e1, e1, __builtin_fmaf(e0, e0, lacc));
+            *reinterpret_cast<float2*>(&S.y[smp * ZSTRIDE + 2 * g]) =
+                make_float2(live ? e0 * a.dscale : 0.0f, live ? e1 * a.dscale : 0.0f);
+        }
+        __syncthreads();
+        {   // D2 = (W3^T dY) * [H2 > 0]
+            const float2 dy = *reinterpret_cast<const float2*>(&S.y[smp * ZSTRIDE + 2 * g]);
+            f32x4 d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t[0], dy.x, (f32x4)0.0f, 0, 0, 0);
+            d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t[1], dy.y, d2, 0, 0, 0);
+            *reinterpret_cast<f32x4*>(&S.d2[own]) = mask4(d2, h2);
+        }
+        if (mb >= 2) {   // dW3^T += H2 dY^T; db3 += 1 dY^T
+            const float* u = S.h2d1 + col0 + 16 * (2 * (mb - 2) + nh);
+            f32x4 s0 = (f32x4)0.0f, s1 = (f32x4)0.0f;
+#pragma unroll
+            for (int j = 0; j < TS / 4; ++j) {
+                const float dy = S.y[(4 * j + g) * ZSTRIDE + n];
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(u[train_row(4 * j)], dy, s0, 0, 0, 0);
+                if (wave == 2) s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, dy, s1, 0, 0, 0);
+            }
+            g3 += s0;
+            gb3 += s1;
+        }
+        __syncthreads();
+        // D1 = (W2^T D2) * [H1 > 0]
+        *reinterpret_cast<f32x4*>(&S.h2d1[own]) =
+            mask4(train_chain(&S.w2t[4 * mb], S.d2 + row0, lane, (f32x4)0.0f), h1);
+        {   // dW2 += D2 H1^T over the samples
+            const float *u = S.d2 + col0 + 16 * mb, *x = S.h1 + col0 + 32 * nh;
+            f32x4 s0 = (f32x4)0.0f, s1 = (f32x4)0.0f;
+#pragma unroll
+            for (int j = 0; j < TS / 4; ++j) {
+                const float d = u[train_row(4 * j)];
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(d, x[train_row(4 * j)], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(d, x[train_row(4 * j) + 16], s1, 0, 0, 0);
+            }
+            g20 += s0;
+            g21 += s1;
+        }
+        __syncthreads();
+        if (mb == 1) {   // dZ = W1^T D1, scattered by the next tile's gather threads
+            const f32x4 dz = train_chain(S.w1t, S.h2d1 + row0, lane, (f32x4)0.0f);
+            *reinterpret_cast<float2*>(&S.y[smp * ZSTRIDE + 2 * g]) = make_float2(dz[0], dz[1]);
+        }
+        {   // dW1 += D1 Z^T and db1 += D1 1, or db2 += D2 1 (column 8)
+            const float* u = (nh ? S.d2 : S.h2d1) + col0 + 16 * mb;
+            f32x4 s0 = (f32x4)0.0f;
+#pragma unroll
+            for (int j = 0; j < TS / 4; ++j)
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(u[train_row(4 * j)], S.z[buf][(4 * j + g) * ZSTRIDE + n], s0, 0,
+                                                          0, 0);
+            g1 += s0;
+        }
+        buf ^= 1;
     }
-    if (t == 0) out[NPARAM] = sRed[0];
+    __syncthreads();
+    if (latents) train_scatter(a, prev, S.y[s8 * ZSTRIDE + c8]);
+    // row 4g + r of a product is unit 4r + g of its block, column n unit unit_of_row(n)
+    float* out = a.partial + (int64_t)blockIdx.x * PSTRIDE;
+    const int col = unit_of_row(n), ch = 4 * (n % 2) + n / 2;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int u = 16 * mb + 4 * r + g;
+        out[OFF_W2 + u * NH + 32 * nh + col] = g20[r];
+        out[OFF_W2 + u * NH + 32 * nh + 16 + col] = g21[r];
+        if (nh == 0 && n < NL) out[OFF_W1 + u * NL + ch] = g1[r];
+        if (n == 8) out[(nh ? OFF_B2 : OFF_B1) + u] = g1[r];
+        if (mb >= 2 && n < NL) out[OFF_W3 + ch * NH + 16 * (2 * (mb - 2) + nh) + 4 * r + g] = g3[r];
+    }
+    if (wave == 2 && lane < NO) out[OFF_B3 + ch] = gb3[0];
+    if (mb == 0) {
+        for (int off = 32; off > 0; off >>= 1) lacc += __shfl_xor(lacc, off);
+        if (lane == 0) S.t[nh] = lacc;
+    }
+    __syncthreads();
+    if (t == 0) out[NPARAM] = S.t[0] + S.t[1];
 }
 
-// Sum of the per-block partials in a fixed order (reproducible): stage 1
-// sums consecutive groups of RGROUP blocks, stage 2 sums the group totals.
+// One Adam step of a value (beta1 = 0.9, beta2 = 0.999, eps = 1e-8, c1 and c2
+// the bias corrections).
+__device__ __forceinline__ void adam(float& p, float g, float& m, float& v, float lr, float c1, float c2)
+{
+    m = 0.9f * m + 0.1f * g;
+    v = 0.999f * v + 0.001f * g * g;
+    p -= lr * (m * c1) / (sqrtf(v * c2) + 1e-8f);
+}
+
+struct UpdateArgs {
+    const float* partial;   // nblocks rows of PSTRIDE
+    int32_t nblocks;
+    float* g_mlp;           // written when the MLP is not stepped (mlp null)
+    float *mlp, *m_mlp, *v_mlp;
+    float *lat, *g_lat, *m_lat, *v_lat;   // nlat4 groups of four
+    int32_t nlat4;
+    float* loss;            // nullable
+    float loss_scale, lr_mlp, lr_lat, c1, c2;
+};
+
+// After a pass, in one launch: the first UPDATE_MLP blocks sum the pass's
+// per-block partials (64 values each; groups of RGROUP rows in row order, one
+// group after another per wave, then the groups in order, so reproducible)
+// and step the MLP with the result, the others step the latents, clearing the
+// gradient they consumed.  Bound by memory (32 bytes moved per latent); two
+// sums and two steps took four launches and 32 us a step, of which this takes
+// 12 (512^2 latents).
 constexpr int RGROUP = 32;
+constexpr int UBLOCK = 512, UWAVES = UBLOCK / 64;
+constexpr int UPDATE_MLP = (PSTRIDE + 63) / 64;
 
-__global__ void k_ntex_reduce1(const float* __restrict__ partial, int nblocks, float* __restrict__ group_sums)
+__global__ __launch_bounds__(UBLOCK) void k_ntex_update(UpdateArgs a)
 {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    int g = blockIdx.y;
-    if (p >= PSTRIDE) return;
+    if (blockIdx.x >= UPDATE_MLP) {
+        const int32_t e = (int32_t)(blockIdx.x - UPDATE_MLP) * UBLOCK + (int32_t)threadIdx.x;
+        if (e >= a.nlat4) return;
+        f32x4 p = reinterpret_cast<f32x4*>(a.lat)[e], m = reinterpret_cast<f32x4*>(a.m_lat)[e],
+              v = reinterpret_cast<f32x4*>(a.v_lat)[e];
+        const f32x4 g = reinterpret_cast<f32x4*>(a.g_lat)[e];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float pk = p[k], mk = m[k], vk = v[k];
+            adam(pk, g[k], mk, vk, a.lr_lat, a.c1, a.c2);
+            p[k] = pk;
+            m[k] = mk;
+            v[k] = vk;
+        }
+        reinterpret_cast<f32x4*>(a.lat)[e] = p;
+        reinterpret_cast<f32x4*>(a.m_lat)[e] = m;
+        reinterpret_cast<f32x4*>(a.v_lat)[e] = v;
+        reinterpret_cast<f32x4*>(a.g_lat)[e] = (f32x4)0.0f;
+        return;
+    }
+    __shared__ float sums[TRAIN_BLOCKS / RGROUP][64];
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int p = (int)blockIdx.x * 64 + lane, ngroups = (a.nblocks + RGROUP - 1) / RGROUP;
+    for (int k = wave; k < ngroups; k += UWAVES) {
+        float s = 0.0f;
+        const int b1 = min(a.nblocks, (k + 1) * RGROUP);
+        if (p < PSTRIDE) {
+#pragma unroll 16
+            for (int b = k * RGROUP; b < b1; ++b) s += a.partial[(int64_t)b * PSTRIDE + p];
+        }
+        sums[k][lane] = s;
+    }
+    __syncthreads();
+    if (wave != 0 || p >= PSTRIDE) return;
     float s = 0.0f;
-    int b1 = min(nblocks, (g + 1) * RGROUP);
-    for (int b = g * RGROUP; b < b1; ++b) s += partial[(int64_t)b * PSTRIDE + p];
-    group_sums[(int64_t)g * PSTRIDE + p] = s;
-}
-
-__global__ void k_ntex_reduce2(const float* __restrict__ group_sums, int ngroups, float* __restrict__ g_mlp,
-                               float* __restrict__ loss, float loss_scale)
-{
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= PSTRIDE) return;
-    float s = 0.0f;
-    for (int g = 0; g < ngroups; ++g) s += group_sums[(int64_t)g * PSTRIDE + p];
-    if (p < NPARAM) g_mlp[p] = s;
-    else if (loss) *loss = s * loss_scale;
-}
-
-// Adam (beta1 = 0.9, beta2 = 0.999, eps = 1e-8, bias-corrected); clears the
-// gradient it consumed.
-__global__ void k_adam(float* __restrict__ param, float* __restrict__ grad, float* __restrict__ m,
-                       float* __restrict__ v, int64_t n, float lr, float c1, float c2)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    float g = grad[e];
-    float mm = 0.9f * m[e] + 0.1f * g;
-    float vv = 0.999f * v[e] + 0.001f * g * g;
-    m[e] = mm;
-    v[e] = vv;
-    param[e] -= lr * (mm * c1) / (sqrtf(vv * c2) + 1e-8f);
-    grad[e] = 0.0f;
+    for (int k = 0; k < ngroups; ++k) s += sums[k][lane];
+    if (p == NPARAM) {
+        if (a.loss) *a.loss = s * a.loss_scale;
+    } else if (a.mlp) {
+        float pk = a.mlp[p], mk = a.m_mlp[p], vk = a.v_mlp[p];
+        adam(pk, s, mk, vk, a.lr_mlp, a.c1, a.c2);
+        a.mlp[p] = pk;
+        a.m_mlp[p] = mk;
+        a.v_mlp[p] = vk;
+    } else {
+        a.g_mlp[p] = s;
+    }
 }
 
 __global__ void k_fill(float* __restrict__ p, int64_t n, float v)
@@ -821,8 +917,7 @@ struct stf_neural {
     float* v_mlp;
     float* g_lat;
     float* g_mlp;
-    float* partial;
-    int32_t partial_blocks;
+    float* partial;   // TRAIN_BLOCKS rows of PSTRIDE
     int64_t step;
     uint16_t* quad16;
     Packed* packed;
@@ -863,29 +958,13 @@ hipError_t fill(float* p, int64_t n, float v, hipStream_t s)
     return hipGetLastError();
 }
 
-constexpr int TRAIN_BLOCKS = 512;   // one resident set: two 80 KiB blocks per CU
-
-stf_status ensure_partial(stf_neural* nt, int32_t blocks)
-{
-    if (nt->partial && nt->partial_blocks >= blocks) return STF_OK;
-    if (nt->partial) {
-        (void)hipDeviceSynchronize();
-        (void)hipFree(nt->partial);
-        nt->partial = nullptr;
-    }
-    size_t groups = ((size_t)blocks + RGROUP - 1) / RGROUP;
-    stf_status s = dalloc((void**)&nt->partial, ((size_t)blocks + groups) * PSTRIDE * 4, "gradient partials");
-    nt->partial_blocks = s == STF_OK ? blocks : 0;
-    return s;
-}
-
-// One forward/backward pass over a batch; leaves the MLP gradient in g_mlp,
-// the latent gradient accumulated in g_lat and the loss in *loss.
+// One forward/backward pass over a batch: per-block MLP gradients and losses
+// in nt->partial (*blocks rows), the latent gradient accumulated in g_lat.
 hipError_t run_fwd_bwd(stf_neural* nt, const float* target, const int32_t* pos, int32_t B, uint32_t kstep,
-                       float* loss, hipStream_t s)
+                       int32_t* blocks, hipStream_t s)
 {
-    int32_t blocks = (B + TS - 1) / TS;
-    if (blocks > nt->partial_blocks) blocks = nt->partial_blocks;
+    const int32_t tiles = (B - 1) / TS + 1;
+    *blocks = tiles < TRAIN_BLOCKS ? tiles : TRAIN_BLOCKS;
     TrainArgs a;
     a.lat = nt->lat;
     a.mlp = nt->mlp;
@@ -902,13 +981,37 @@ hipError_t run_fwd_bwd(stf_neural* nt, const float* target, const int32_t* pos, 
     a.dscale = 2.0f / (8.0f * (float)B);
     a.g_lat = nt->g_lat;
     a.partial = nt->partial;
-    hipLaunchKernelGGL(k_ntex_train, dim3(blocks), dim3(TBLOCK), 0, s, a);
-    int ngroups = (blocks + RGROUP - 1) / RGROUP;
-    float* group_sums = nt->partial + (int64_t)nt->partial_blocks * PSTRIDE;
-    hipLaunchKernelGGL(k_ntex_reduce1, dim3((PSTRIDE + 255) / 256, ngroups), dim3(256), 0, s, nt->partial, blocks,
-                       group_sums);
-    hipLaunchKernelGGL(k_ntex_reduce2, dim3((PSTRIDE + 255) / 256), dim3(256), 0, s, group_sums, ngroups, nt->g_mlp,
-                       loss, 1.0f / (8.0f * (float)B));
+    hipLaunchKernelGGL(k_ntex_train, dim3(*blocks), dim3(TBLOCK), 0, s, a);
+    return hipGetLastError();
+}
+
+// Sums a pass's partials: into g_mlp, or (step) straight into Adam steps of
+// the MLP and the latents.
+hipError_t run_update(stf_neural* nt, int32_t blocks, int32_t B, float* loss, bool step, float lr_lat, float lr_mlp,
+                      float c1, float c2, hipStream_t s)
+{
+    UpdateArgs a = {};
+    a.partial = nt->partial;
+    a.nblocks = blocks;
+    a.g_mlp = nt->g_mlp;
+    a.loss = loss;
+    a.loss_scale = 1.0f / (8.0f * (float)B);
+    if (step) {
+        a.mlp = nt->mlp;
+        a.m_mlp = nt->m_mlp;
+        a.v_mlp = nt->v_mlp;
+        a.lat = nt->lat;
+        a.g_lat = nt->g_lat;
+        a.m_lat = nt->m_lat;
+        a.v_lat = nt->v_lat;
+        a.nlat4 = (int32_t)(nlat(nt) / 4);   // below 2^28
+        a.lr_mlp = lr_mlp;
+        a.lr_lat = lr_lat;
+        a.c1 = c1;
+        a.c2 = c2;
+    }
+    hipLaunchKernelGGL(k_ntex_update, dim3((unsigned)(UPDATE_MLP + (a.nlat4 + UBLOCK - 1) / UBLOCK)), dim3(UBLOCK), 0, s,
+                       a);
     return hipGetLastError();
 }
 
@@ -973,7 +1076,7 @@ stf_status stf_ntex_create(int32_t tex_w, int32_t tex_h, int32_t lat_w, int32_t 
     if (s == STF_OK)
         s = dalloc((void**)&nt->quad16, (size_t)(lat_w + 1) * (lat_h + 1) * 4 * NL * 2, "binary16 corner quads");
     if (s == STF_OK) s = dalloc((void**)&nt->packed, sizeof(Packed), "packed weights");
-    if (s == STF_OK) s = ensure_partial(nt, TRAIN_BLOCKS);
+    if (s == STF_OK) s = dalloc((void**)&nt->partial, (size_t)TRAIN_BLOCKS * PSTRIDE * 4, "gradient partials");
     if (s == STF_OK) {
         hipError_t e = hipMemcpy(nt->lat, latents_host, lb, hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(nt->mlp, mlp_host, NPARAM * 4, hipMemcpyHostToDevice);
@@ -1015,15 +1118,11 @@ stf_status stf_ntex_train(stf_neural* nt, const float* target_dev, int32_t steps
     for (int32_t k = 0; k < steps; ++k) {
         nt->step += 1;
         double c1 = 1.0 / (1.0 - pow(0.9, (double)nt->step)), c2 = 1.0 / (1.0 - pow(0.999, (double)nt->step));
-        hipError_t e = run_fwd_bwd(nt, target_dev, nullptr, batch, pcg(key ^ (uint32_t)nt->step),
-                                   loss_dev ? loss_dev + k : nullptr, st);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_adam, dim3((NPARAM + 255) / 256), dim3(256), 0, st, nt->mlp, nt->g_mlp, nt->m_mlp,
-                               nt->v_mlp, (int64_t)NPARAM, lr_mlp, (float)c1, (float)c2);
-            hipLaunchKernelGGL(k_adam, dim3((unsigned)((nlat(nt) + 255) / 256)), dim3(256), 0, st, nt->lat,
-                               nt->g_lat, nt->m_lat, nt->v_lat, nlat(nt), lr_latent, (float)c1, (float)c2);
-            e = hipGetLastError();
-        }
+        int32_t blocks = 0;
+        hipError_t e = run_fwd_bwd(nt, target_dev, nullptr, batch, pcg(key ^ (uint32_t)nt->step), &blocks, st);
+        if (e == hipSuccess)
+            e = run_update(nt, blocks, batch, loss_dev ? loss_dev + k : nullptr, true, lr_latent, lr_mlp, (float)c1,
+                           (float)c2, st);
         if (e != hipSuccess) return stf_fail(STF_E_DEVICE, "training launch failed: %s", hipGetErrorString(e));
     }
     nt->ready = false;
@@ -1045,7 +1144,9 @@ stf_status stf_ntex_gradients(stf_neural* nt, const float* target_dev, const int
     if (s != STF_OK) return s;
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = fill(nt->g_lat, nlat(nt), 0.0f, st);
-    if (e == hipSuccess) e = run_fwd_bwd(nt, target_dev, positions_dev, batch, 0u, loss_dev, st);
+    int32_t blocks = 0;
+    if (e == hipSuccess) e = run_fwd_bwd(nt, target_dev, positions_dev, batch, 0u, &blocks, st);
+    if (e == hipSuccess) e = run_update(nt, blocks, batch, loss_dev, false, 0.0f, 0.0f, 0.0f, 0.0f, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(grad_latents_dev, nt->g_lat, (size_t)nlat(nt) * 4, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(grad_mlp_dev, nt->g_mlp, NPARAM * 4, hipMemcpyDeviceToDevice, st);
