@@ -235,6 +235,37 @@ __device__ __forceinline__ float load_texel(const void* __restrict__ base, int64
     return 0.0f;
 }
 
+// N consecutive stored values from p, which is aligned to one value only: the
+// fewest loads the size allows (dword loads need no more than byte alignment).
+template <int FMT, int N>
+struct TexelRun {
+    static constexpr int BYTES = N * fmt_bytes(FMT);
+    uint32_t w[(BYTES + 3) / 4];
+    __device__ __forceinline__ void load(const void* p)
+    {
+        const uint8_t* q = static_cast<const uint8_t*>(p) + BYTES / 4 * 4;
+        if constexpr (BYTES >= 4) __builtin_memcpy(w, p, BYTES / 4 * 4);
+        if constexpr (BYTES % 4 == 1) w[BYTES / 4] = *q;
+        if constexpr (BYTES % 4 >= 2) {
+            uint16_t h;
+            __builtin_memcpy(&h, q, 2);
+            w[BYTES / 4] = h;
+        }
+        if constexpr (BYTES % 4 == 3) w[BYTES / 4] |= (uint32_t)q[2] << 16;
+    }
+    // Value k (a constant after unrolling), decoded exactly; RAW: U8 as its code 0..255.
+    template <bool RAW = false>
+    __device__ __forceinline__ float value(int k) const
+    {
+        if constexpr (FMT == F32) return __builtin_bit_cast(float, w[k]);
+        if constexpr (FMT == F16) return dec_f16((uint16_t)(w[k / 2] >> (16 * (k % 2))));
+        if constexpr (FMT == BF16) return dec_bf16((uint16_t)(w[k / 2] >> (16 * (k % 2))));
+        if constexpr (FMT == FP8_E4M3) return dec_e4m3((w[k / 4] >> (8 * (k % 4))) & 0xffu);
+        const uint32_t code = (w[k / 4] >> (8 * (k % 4))) & 0xffu;
+        return RAW ? (float)code : dec_u8(code);
+    }
+};
+
 constexpr int32_t BAD_INDEX = (int32_t)0x80000000;
 
 }  // namespace stf

@@ -34,33 +34,39 @@ __device__ __forceinline__ int clampi(int v, int hi)
     return v < 0 ? 0 : (v > hi ? hi : v);
 }
 
-// All C channels of texel (x, y) (already clamped).
-template <int FMT, int C>
-__device__ __forceinline__ void load_rgba(const TexLevel& L, int x, int y, float (&v)[C])
-{
-    int64_t e = ((int64_t)y * L.w + x) * C;
-    if constexpr (FMT == F32 && C == 4) {
-        float4 f = reinterpret_cast<const float4*>(L.texels)[e >> 2];
-        v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
-    } else if constexpr (FMT == F32 && C == 2) {
-        float2 f = reinterpret_cast<const float2*>(L.texels)[e >> 1];
-        v[0] = f.x; v[1] = f.y;
-    } else {
-#pragma unroll
-        for (int c = 0; c < C; ++c) v[c] = load_texel<FMT>(L.texels, e + c);
-    }
-}
-
-// Stored texels: C channels of format FMT.
+// Stored texels: C channels of format FMT, row-major.  A texel, or a row of
+// neighbouring texels, is read with as few loads as its size allows.
 template <int FMT, int C>
 struct DenseSrc {
     static constexpr int CAP = C;
     static constexpr bool DECODES = false;   // a texel is a plain load
+    static constexpr bool WINDOWS = true;    // rows of taps are contiguous
+    static constexpr int FORMAT = FMT;
+    // Deterministic sums take U8 codes as they are and divide the sum by 255:
+    // one instruction a value to decode, and the sum's own rounding only.
+    static constexpr float RAW_SCALE = FMT == U8 ? 255.0f : 1.0f;
     TexLevel L;
     __device__ int w() const { return L.w; }
     __device__ int h() const { return L.h; }
     __device__ int channels() const { return C; }
-    __device__ void load(int x, int y, float (&v)[CAP]) const { load_rgba<FMT, C>(L, x, y, v); }
+    __device__ __forceinline__ const void* at(int x, int y) const
+    {
+        return static_cast<const char*>(L.texels) + ((int64_t)y * L.w + x) * (C * fmt_bytes(FMT));
+    }
+    __device__ void load(int x, int y, float (&v)[CAP]) const
+    {
+        TexelRun<FMT, C> t;
+        t.load(at(x, y));
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = t.value(c);
+    }
+    __device__ void load_raw(int x, int y, float (&v)[CAP]) const
+    {
+        TexelRun<FMT, C> t;
+        t.load(at(x, y));
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = t.template value<true>(c);
+    }
 };
 
 // Material texels (8 bytes: albedo RGB UNORM8, roughness UNORM8, tangent
@@ -69,6 +75,8 @@ struct DenseSrc {
 struct MaterialSrc {
     static constexpr int CAP = 6;
     static constexpr bool DECODES = false;
+    static constexpr bool WINDOWS = false;
+    static constexpr float RAW_SCALE = 1.0f;
     TexLevel L;
     __device__ int w() const { return L.w; }
     __device__ int h() const { return L.h; }
@@ -83,6 +91,7 @@ struct MaterialSrc {
         v[4] = dec_f16((uint16_t)(t.y & 0xffffu));
         v[5] = dec_f16((uint16_t)(t.y >> 16));
     }
+    __device__ void load_raw(int x, int y, float (&v)[CAP]) const { load(x, y, v); }
 };
 
 // DCT blocks: CAP words per block (a multiple of 4), C <= CAP channels used.
@@ -323,28 +332,93 @@ __global__ __launch_bounds__(BLOCK) void k_tex2d_deterministic(Src S, const floa
     cy += axis_weights_scaled<KIND>(ty, wy);
 #pragma unroll
     for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
-    // Wide sources (materials, six channels) keep one row of taps in flight:
-    // unrolling all rows would hold every tap's texel at once.
-    constexpr int ROWS_UNROLLED = CAP > 4 ? 1 : NT;
-#pragma unroll ROWS_UNROLLED
-    for (int b = 0; b < NT; ++b) {
-        int yy = clampi(cy + b, S.h() - 1);
-        float row[CAP];
+    // A row of NT taps is read whole, as the run of NT texels that holds every
+    // tap the clamping leaves (from column xs): 4 loads of 16 bytes for 8-bit
+    // RGBA and 16 taps instead of 64 of a byte each with their addresses.
+    // Only where a lane of the wave has a tap to clamp, the texels of a row
+    // are moved to their taps (taps left of the run take its first texel,
+    // taps right of it its last).  Otherwise (tiled materials, textures
+    // narrower than a row) every tap is loaded by itself; the values and the
+    // order of the sum are the same.  2M pixels of a frame, 4096^2 8-bit RGBA,
+    // bicubic: 59 us (loads and decoding) -> 20 us (half of it the streams);
+    // scattered over 4096^2 binary32 RGBA: 332 -> 205 us (its lines); over 50
+    // columns of one bfloat16 channel, every wave at a border: 31 -> 17 us.
+    bool whole = false;
+    if constexpr (Src::WINDOWS) whole = S.w() >= NT;
+    if (whole) {
+        if constexpr (Src::WINDOWS) {
+            const int xs = clampi(cx, S.w() - NT), d = cx - xs;
+            const bool clamps = __any(d != 0);
+            TexelRun<Src::FORMAT, NT * CAP> run[NT];
 #pragma unroll
-        for (int c = 0; c < CAP; ++c) row[c] = 0.0f;
+            for (int b = 0; b < NT; ++b) run[b].load(S.at(xs, clampi(cy + b, S.h() - 1)));
 #pragma unroll
-        for (int a = 0; a < NT; ++a) {
-            float v[CAP];
-            S.load(clampi(cx + a, S.w() - 1), yy, v);
+            for (int b = 0; b < NT; ++b) {
+                float t[NT][CAP];
 #pragma unroll
-            for (int c = 0; c < CAP; ++c) row[c] = __builtin_fmaf(wx[a], v[c], row[c]);
+                for (int a = 0; a < NT; ++a)
+#pragma unroll
+                    for (int c = 0; c < CAP; ++c) t[a][c] = run[b].template value<true>(a * CAP + c);
+                if (clamps) {
+#pragma unroll
+                    for (int c = 0; c < CAP; ++c) {
+                        if constexpr (NT == 4) {
+                            const bool l1 = d == 1 || d >= 3, l2 = d >= 2, r1 = d == -1 || d <= -3, r2 = d <= -2;
+                            t[0][c] = l1 ? t[1][c] : t[0][c];
+                            t[1][c] = l1 ? t[2][c] : t[1][c];
+                            t[2][c] = l1 ? t[3][c] : t[2][c];
+                            t[0][c] = l2 ? t[2][c] : t[0][c];
+                            t[1][c] = l2 ? t[3][c] : t[1][c];
+                            t[2][c] = l2 ? t[3][c] : t[2][c];
+                            t[3][c] = r1 ? t[2][c] : t[3][c];
+                            t[2][c] = r1 ? t[1][c] : t[2][c];
+                            t[1][c] = r1 ? t[0][c] : t[1][c];
+                            t[3][c] = r2 ? t[1][c] : t[3][c];
+                            t[2][c] = r2 ? t[0][c] : t[2][c];
+                            t[1][c] = r2 ? t[0][c] : t[1][c];
+                        } else {
+                            const float t0 = t[0][c];
+                            t[0][c] = d >= 1 ? t[1][c] : t0;
+                            t[1][c] = d <= -1 ? t0 : t[1][c];
+                        }
+                    }
+                }
+                float row[CAP];
+#pragma unroll
+                for (int c = 0; c < CAP; ++c) row[c] = 0.0f;
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+#pragma unroll
+                    for (int c = 0; c < CAP; ++c) row[c] = __builtin_fmaf(wx[a], t[a][c], row[c]);
+#pragma unroll
+                for (int c = 0; c < CAP; ++c) acc[c] = __builtin_fmaf(wy[b], row[c], acc[c]);
+            }
         }
+    } else {
+        // Wide sources (materials, six channels) keep one row of taps in
+        // flight: unrolling all rows would hold every tap's texel at once.
+        constexpr int ROWS_UNROLLED = CAP > 4 ? 1 : NT;
+#pragma unroll ROWS_UNROLLED
+        for (int b = 0; b < NT; ++b) {
+            int yy = clampi(cy + b, S.h() - 1);
+            float row[CAP];
 #pragma unroll
-        for (int c = 0; c < CAP; ++c) acc[c] = __builtin_fmaf(wy[b], row[c], acc[c]);
+            for (int c = 0; c < CAP; ++c) row[c] = 0.0f;
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                float v[CAP];
+                S.load_raw(clampi(cx + a, S.w() - 1), yy, v);
+#pragma unroll
+                for (int c = 0; c < CAP; ++c) row[c] = __builtin_fmaf(wx[a], v[c], row[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < CAP; ++c) acc[c] = __builtin_fmaf(wy[b], row[c], acc[c]);
+        }
     }
-    constexpr float S2 = axis_scale<KIND>() * axis_scale<KIND>();   // 36 (B-spline), 4 (Keys), 324 (Mitchell)
+    // 36 (B-spline), 4 (Keys), 324 (Mitchell), by the 255 of U8 codes
+    constexpr float S2 = axis_scale<KIND>() * axis_scale<KIND>() * Src::RAW_SCALE;
 #pragma unroll
-    for (int c = 0; c < CAP; ++c) acc[c] = !ok ? __builtin_nanf("") : (KIND == KIND_LINEAR ? acc[c] : acc[c] / S2);
+    for (int c = 0; c < CAP; ++c) acc[c] = !ok ? __builtin_nanf("") : (S2 == 1.0f ? acc[c] : acc[c] / S2);
     block_store(S, out, n, live, oi, acc, order && scatter);
 }
 
