@@ -587,13 +587,6 @@ __device__ __forceinline__ float det_taps(const GridView& g, const int (&base)[3
     return acc;
 }
 
-template <int FMT, int KIND>
-__device__ __forceinline__ float det_sum_global(const GridView& g, const int (&base)[3], const float (&w)[3][4])
-{
-    int32_t leaf[8];
-    return det_leaves<KIND>(g, base, leaf) ? det_taps<FMT, KIND>(g, base, leaf, w) : det_background<KIND>(g, w);
-}
-
 // Cell, first tap and scaled per-axis weights of a query; false if the
 // position has no cell (R10: non-finite or too large).
 template <int KIND>
@@ -630,8 +623,12 @@ __global__ __launch_bounds__(BLOCK, 8) void k_grid_det_linear(GridView g, const 
     int base[3];
     float w[3][4];
     const bool ok = det_setup<KIND_LINEAR>(p, base, w);
-    __builtin_nontemporal_store(ok ? det_unscale<KIND_LINEAR>(det_sum_global<FMT, KIND_LINEAR>(g, base, w))
-                                   : __builtin_nanf(""), out + ((order && scatter) ? order[i] : i));
+    int32_t leaf[8];
+    float sum = 0.0f;
+    if (ok)
+        sum = det_leaves<KIND_LINEAR>(g, base, leaf) ? det_taps<FMT, KIND_LINEAR>(g, base, leaf, w)
+                                                     : det_background<KIND_LINEAR>(g, w);
+    __builtin_nontemporal_store(ok ? sum : __builtin_nanf(""), out + ((order && scatter) ? order[i] : i));
 }
 
 // Orders this wave's LDS accesses before and after it (the LDS serves a
@@ -666,10 +663,11 @@ __device__ __forceinline__ float fma_quad(float v, float w, float acc)
         w, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true)), acc);
 }
 
-// Deterministic filtering with the 64-tap kinds from global memory.
+// The unscaled sums of a wave's queries (one per lane, those with `taps`, whose
+// tap block meets a stored leaf of leaf[]) over the 64 taps of a cubic kind,
+// from global memory; S: the wave's 64 slots.  Every lane of the wave calls it.
 //
-// First a thread per query: weights, the leaves its tap block meets (det_leaves)
-// and, in empty space, the background's sum.  The wave then packs its queries
+// The wave packs its queries
 // that meet a leaf into LDS slots and sums 16 of them at a time, four lanes
 // each: lane y takes the rows y of the four planes, so that one load
 // instruction of a query's four lanes covers up to 64 contiguous bytes of a
@@ -682,9 +680,8 @@ __device__ __forceinline__ float fma_quad(float v, float w, float acc)
 // 8M samples of whole rays, whose waves now sum only their live queries: 112 ->
 // 97 us.
 template <int FMT, int KIND>
-__global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
-    GridView g, const float* __restrict__ q, int32_t n, float* __restrict__ out, const int32_t* __restrict__ order,
-    int scatter)
+__device__ __forceinline__ float det_wave(const GridView& g, const int (&base)[3], const float (&w)[3][4],
+                                          const int32_t (&leaf)[8], bool taps, DetSlot* __restrict__ S)
 {
     constexpr int NT = 4;
     constexpr uint32_t TB = FMT == F32 ? 4u : (FMT == F16 || FMT == BF16 ? 2u : 1u);
@@ -692,22 +689,10 @@ __global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
     using Chunk = typename std::conditional<TB == 1u, uint2, uint4>::type;
     // a stored leaf reaches out of the domain only along axes that end inside a leaf
     const bool edges = ((g.dx | g.dy | g.dz) & 7) != 0;
-    __shared__ DetSlot slots[BLOCK];
     const int lane = threadIdx.x % 64;
-    DetSlot* __restrict__ S = slots + threadIdx.x / 64 * 64;
-    const int32_t i = blockIdx.x * BLOCK + threadIdx.x;
-    const bool live = i < n;
-    float result = __builtin_nanf("");
+    float result = 0.0f;
     int rank = -1, count;
     {
-        const int32_t src = live ? i : 0;
-        const float p[3] = {q[3 * (int64_t)src], q[3 * (int64_t)src + 1], q[3 * (int64_t)src + 2]};
-        int base[3] = {0, 0, 0};
-        float w[3][4];
-        const bool ok = det_setup<KIND>(p, base, w) && live;
-        int32_t leaf[8];
-        const bool taps = ok && det_leaves<KIND>(g, base, leaf);
-        if (ok && !taps) result = det_background<KIND>(g, w);
         const uint64_t mask = __ballot(taps);
         count = __popcll(mask);
         // Neighbouring queries whose taps begin in the same block of 4x4x4
@@ -721,8 +706,7 @@ __global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
         if (shared * 16 > count * 10) {
             if (taps) result = det_taps<FMT, KIND>(g, base, leaf, w);
             count = 0;
-        } else
-        if (taps) {
+        } else if (taps) {
             rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
             DetSlot s;
             const uint32_t xo0 = (uint32_t)(base[0] & 7 & ~(CV - 1));
@@ -807,51 +791,90 @@ __global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
         if (y == 0) S[slot].w[0][0] = acc;
     }
     wave_lds_fence();
+    return rank >= 0 ? S[rank].w[0][0] : result;
+}
+
+template <int FMT, int KIND>
+__global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
+    GridView g, const float* __restrict__ q, int32_t n, float* __restrict__ out, const int32_t* __restrict__ order,
+    int scatter)
+{
+    __shared__ DetSlot slots[BLOCK];
+    const int32_t i = blockIdx.x * BLOCK + threadIdx.x;
+    const bool live = i < n;
+    const int32_t src = live ? i : 0;
+    const float p[3] = {q[3 * (int64_t)src], q[3 * (int64_t)src + 1], q[3 * (int64_t)src + 2]};
+    int base[3] = {0, 0, 0};
+    float w[3][4];
+    const bool ok = det_setup<KIND>(p, base, w);
+    int32_t leaf[8];
+    const bool taps = ok && live && det_leaves<KIND>(g, base, leaf);
+    float sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, slots + threadIdx.x / 64 * 64);
     if (!live) return;
-    if (rank >= 0) result = S[rank].w[0][0];
-    __builtin_nontemporal_store(det_unscale<KIND>(result), out + ((order && scatter) ? order[i] : i));
+    if (!taps) sum = det_background<KIND>(g, w);   // empty space
+    __builtin_nontemporal_store(ok ? det_unscale<KIND>(sum) : __builtin_nanf(""),
+                                out + ((order && scatter) ? order[i] : i));
 }
 
 // ---------------------------------------------------------------------------
 // deterministic filtering of a sorted stream with the block's taps staged in
 // LDS.  Queries that are neighbours in Morton order share most of their tap
-// blocks, so a block reads every voxel of the bounding box of its queries'
-// tap blocks once and then filters each query from LDS: the box's leaf slots
-// are resolved first (one walk per slot), then each voxel is one load.  A
-// block stages only when that pays: the box holds at most STAGE_VOXELS
-// voxels in at most STAGE_SLOTS leaf slots, its queries read at least
-// STAGE_REUSE taps per staged voxel, and some slot holds a leaf; otherwise it
-// filters from global memory (where all-empty tap blocks cost no loads).
-// Both paths read the same texel values and sum them in the same order, so
-// the results are the same.
+// blocks, so a block reads the voxels of the bounding box of its queries' tap
+// blocks once and then filters each query from LDS, where that pays: the box
+// fits the tile and lies in at most STAGE_SLOTS leaf slots, its queries read
+// at least STAGE_REUSE taps per voxel of it, and some slot holds a leaf;
+// otherwise it filters from global memory.  The box's leaf slots are resolved
+// first (one walk per slot), for either way; the box is staged in chunks of
+// four voxels along x (one load and one 16-byte LDS write each, from the chunk
+// that holds its first column on, so its rows are up to 3 voxels longer on
+// either side).  Both ways read the same texel values and sum them in the same
+// order, so the results are the same.
+//
+// Bound by VALU issue (about 900 instructions per wave).  4.2M samples in the
+// medium of a 512^3 grid, sorted (a quarter of the blocks stage): binary16 140
+// us with one load and its address per staged voxel and a walk per query, 110
+// us so; binary32 149 and 117 us.
 // ---------------------------------------------------------------------------
-constexpr int STAGE_VOXELS = 4096;   // 16 KiB of binary32 per block
+
+// Without staging, binary32 queries are summed by four lanes each (det_wave,
+// whose slots take the tile's place), narrower ones, whose lines hold more
+// voxels, by a lane each (that way round binary32 took 124, binary16 123 us).
+template <int FMT>
+constexpr bool STAGE_QUADS = FMT == F32;
+// 24 KiB of binary32 per block, as the slots need, or 18 KiB (8 blocks per CU).
+template <int FMT>
+constexpr int STAGE_VOXELS = STAGE_QUADS<FMT> ? 6144 : 4608;
+static_assert(STAGE_VOXELS<F32> * sizeof(float) >= BLOCK * sizeof(DetSlot), "the tile and the slots share their LDS");
 constexpr int STAGE_SLOTS = 64;
 constexpr int STAGE_REUSE = 4;
 
-__device__ __forceinline__ int wave_min(int v)
+// Four stored values of format FMT at p (aligned to their size).
+template <int FMT>
+__device__ __forceinline__ float4 load_chunk4(const char* p)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-__device__ __forceinline__ int wave_max(int v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-    return v;
+    TexelRun<FMT, 4> t;
+    if constexpr (fmt_bytes(FMT) == 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(p);
+        t.w[0] = v.x; t.w[1] = v.y; t.w[2] = v.z; t.w[3] = v.w;
+    } else if constexpr (fmt_bytes(FMT) == 2) {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        t.w[0] = v.x; t.w[1] = v.y;
+    } else {
+        t.w[0] = *reinterpret_cast<const uint32_t*>(p);
+    }
+    return make_float4(t.value(0), t.value(1), t.value(2), t.value(3));
 }
 
 template <int FMT, int KIND>
-__global__ __launch_bounds__(BLOCK) void k_grid_det_staged(GridView g, const float* __restrict__ q, int32_t n,
+__global__ __launch_bounds__(BLOCK, (STAGE_QUADS<FMT> ? 6 : 8)) void k_grid_det_staged(GridView g, const float* __restrict__ q, int32_t n,
                                                            float* __restrict__ out, const int32_t* __restrict__ order,
                                                            int scatter, unsigned long long* __restrict__ counters)
 {
-    constexpr int NT = KIND == KIND_LINEAR ? 2 : 4;
-    __shared__ float tile[STAGE_VOXELS];
+    constexpr int NT = 4;
+    constexpr int VOXELS = STAGE_VOXELS<FMT>;
+    __shared__ __align__(16) float tile[VOXELS];
     __shared__ int32_t slot_leaf[STAGE_SLOTS];
-    __shared__ int box[6][BLOCK / 64];
+    __shared__ int box[7][BLOCK / 64];
     const int32_t i = blockIdx.x * BLOCK + threadIdx.x;
     const bool live = i < n;
     float p[3] = {0.0f, 0.0f, 0.0f};
@@ -860,20 +883,29 @@ __global__ __launch_bounds__(BLOCK) void k_grid_det_staged(GridView g, const flo
         p[1] = q[3 * (int64_t)i + 1];
         p[2] = q[3 * (int64_t)i + 2];
     }
-    int base[3];
+    int base[3] = {0, 0, 0};
     float w[3][4];
-    const bool ok = live && det_setup<KIND>(p, base, w);
+    const bool ok = det_setup<KIND>(p, base, w) && live;
     // bounding box of the block's tap blocks (queries with a cell only)
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    {
+        int m[6];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int mn = wave_min(ok ? base[a] : INT_MAX), mx = wave_max(ok ? base[a] + NT - 1 : INT_MIN);
+        for (int a = 0; a < 3; ++a) {
+            m[a] = wave_min(ok ? base[a] : INT_MAX);
+            m[3 + a] = wave_min(ok ? -(base[a] + NT - 1) : INT_MAX);
+        }
+        const int cnt = __popcll(__ballot(ok));
         if (lane == 0) {
-            box[a][wave] = mn;
-            box[3 + a][wave] = mx;
+#pragma unroll
+            for (int a = 0; a < 6; ++a) box[a][wave] = m[a];
+            box[6][wave] = cnt;
         }
     }
-    const int nok = __syncthreads_count(ok);
+    __syncthreads();
+    int nok = 0;   // wave-uniform from here on, and the same in every wave
+#pragma unroll
+    for (int k = 0; k < BLOCK / 64; ++k) nok += __builtin_amdgcn_readfirstlane(box[6][k]);
     int lo[3], ext[3], l0[3], nl[3];
     bool fits = nok > 0;
 #pragma unroll
@@ -882,62 +914,87 @@ __global__ __launch_bounds__(BLOCK) void k_grid_det_staged(GridView g, const flo
 #pragma unroll
         for (int k = 1; k < BLOCK / 64; ++k) {
             mn = min(mn, box[a][k]);
-            mx = max(mx, box[3 + a][k]);
+            mx = min(mx, box[3 + a][k]);
         }
+        mn = __builtin_amdgcn_readfirstlane(mn);
+        mx = -__builtin_amdgcn_readfirstlane(mx);
         lo[a] = mn;
         ext[a] = fits ? mx - mn + 1 : 0;   // at most 2^25 + 4: coordinates with a cell are below 2^24
         l0[a] = mn >> 3;
         nl[a] = fits ? (mx >> 3) - l0[a] + 1 : 0;
-        fits = fits && ext[a] <= STAGE_VOXELS && nl[a] <= STAGE_SLOTS;
+        fits = fits && ext[a] <= VOXELS && nl[a] <= STAGE_SLOTS;
     }
     const int64_t vol = (int64_t)ext[0] * ext[1] * ext[2];
     const int nslot = nl[0] * nl[1] * nl[2];
-    // the same decision in every thread of the block
-    bool stage = fits && vol <= STAGE_VOXELS && nslot <= STAGE_SLOTS &&
-                 vol * STAGE_REUSE <= (int64_t)nok * NT * NT * NT;
+    const int x0 = lo[0] & ~3, nch = fits ? ((lo[0] + ext[0] - 1 - x0) >> 2) + 1 : 0;   // chunks of a row
+    // The leaves of the box, one walk per slot, then each query's from there.
+    const bool slots = fits && nslot <= STAGE_SLOTS;   // the same decision in every thread of the block
+    int32_t leaf[8];
     bool taps = false;   // this query's tap block meets a stored leaf
-    if (stage) {
+    if (slots) {
         if ((int)threadIdx.x < nslot) {
             const int sx = l0[0] + (int)threadIdx.x % nl[0], sy = l0[1] + ((int)threadIdx.x / nl[0]) % nl[1],
                       sz = l0[2] + (int)threadIdx.x / (nl[0] * nl[1]);
             slot_leaf[threadIdx.x] = in_domain(g, sx * 8, sy * 8, sz * 8) ? grid_leaf(g, sx * 8, sy * 8, sz * 8) : -1;
         }
         __syncthreads();
-        if (ok) {
+        int at[3][2];   // slots of the first and the last tap along each axis
+        bool nb[3];     // they lie in two leaves
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int sx = ((base[0] + ((k & 1) ? NT - 1 : 0)) >> 3) - l0[0];
-                const int sy = ((base[1] + ((k & 2) ? NT - 1 : 0)) >> 3) - l0[1];
-                const int sz = ((base[2] + ((k & 4) ? NT - 1 : 0)) >> 3) - l0[2];
-                taps = taps || slot_leaf[(sz * nl[1] + sy) * nl[0] + sx] >= 0;
-            }
+        for (int a = 0; a < 3; ++a) {
+            const int stride = a == 0 ? 1 : (a == 1 ? nl[0] : nl[0] * nl[1]);
+            nb[a] = (base[a] & 7) + NT - 1 >= 8;
+            at[a][0] = ok ? ((base[a] >> 3) - l0[a]) * stride : 0;
+            at[a][1] = at[a][0] + (nb[a] ? stride : 0);
         }
-        // staging pays only for the queries that read texels; the others
-        // (empty space) sum the background either way
-        stage = (int64_t)__syncthreads_count(taps) * NT * NT * NT >= vol * STAGE_REUSE;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int32_t l = slot_leaf[ok ? at[0][k & 1] + at[1][(k >> 1) & 1] + at[2][k >> 2] : 0];
+            const bool used = ok && (!(k & 1) || nb[0]) && (!(k & 2) || nb[1]) && (!(k & 4) || nb[2]);
+            leaf[k] = used ? l : -1;
+            taps = taps || leaf[k] >= 0;
+        }
+    } else {
+        taps = ok && det_leaves<KIND>(g, base, leaf);
     }
+    // staging pays only for the queries that read texels; the others (empty
+    // space) sum the background either way
+    bool stage = slots && (int64_t)(4 * nch) * ext[1] * ext[2] <= VOXELS && vol * STAGE_REUSE <= (int64_t)nok * NT * NT * NT;
+    if (stage) stage = (int64_t)__syncthreads_count(taps) * NT * NT * NT >= vol * STAGE_REUSE;
     if (counters && threadIdx.x == 0) {   // {blocks that staged, blocks}, when counting is on
         if (stage) atomicAdd(&counters[0], 1ull);
         atomicAdd(&counters[1], 1ull);
     }
     if (stage) {
-        // voxel v = threadIdx.x + k BLOCK of the box, x fastest; its
+        // chunk c = threadIdx.x + k BLOCK of the box, x fastest; its
         // coordinates advance by those of BLOCK (one carry per axis at most)
-        const int e01 = ext[0] * ext[1];
-        const int sx = BLOCK % ext[0], sy = (BLOCK / ext[0]) % ext[1], sz = BLOCK / e01;
-        int x = (int)threadIdx.x % ext[0], y = ((int)threadIdx.x / ext[0]) % ext[1], z = (int)threadIdx.x / e01;
-        for (int v = threadIdx.x; v < (int)vol; v += BLOCK) {
-            const int vx = lo[0] + x, vy = lo[1] + y, vz = lo[2] + z;
+        const int rows = nch * ext[1], chunks = rows * ext[2];
+        const int sx = BLOCK % nch, sy = (BLOCK / nch) % ext[1], sz = BLOCK / rows;
+        int x = (int)threadIdx.x % nch, y = ((int)threadIdx.x / nch) % ext[1], z = (int)threadIdx.x / rows;
+        const bool edges = ((g.dx | g.dy | g.dz) & 7) != 0;   // a stored leaf may reach out of the domain
+        const char* __restrict__ leaves = reinterpret_cast<const char*>(g.leaves);
+        for (int c = threadIdx.x; c < chunks; c += BLOCK) {
+            const int vx = x0 + 4 * x, vy = lo[1] + y, vz = lo[2] + z;
+            // (a chunk that begins left of the box begins in the box's first leaf)
             const int32_t lf = slot_leaf[((vz >> 3) - l0[2]) * nl[1] * nl[0] + ((vy >> 3) - l0[1]) * nl[0] +
                                          (vx >> 3) - l0[0]];
-            tile[v] = (lf >= 0 && in_domain(g, vx, vy, vz))
-                          ? load_texel<FMT>(g.leaves, (int64_t)lf * 512 + leaf_offset(FMT, vx & 7, vy & 7, vz & 7))
-                          : g.background;
+            float4 t = make_float4(g.background, g.background, g.background, g.background);
+            if (lf >= 0 && (!edges || (vy < g.dy && vz < g.dz))) {
+                t = load_chunk4<FMT>(leaves + ((uint32_t)lf * 512u + leaf_offset(FMT, vx & 7, vy & 7, vz & 7)) *
+                                                  (uint32_t)fmt_bytes(FMT));
+                if (edges) {
+                    t.x = vx < g.dx ? t.x : g.background;
+                    t.y = vx + 1 < g.dx ? t.y : g.background;
+                    t.z = vx + 2 < g.dx ? t.z : g.background;
+                    t.w = vx + 3 < g.dx ? t.w : g.background;
+                }
+            }
+            reinterpret_cast<float4*>(tile)[c] = t;
             x += sx;
             y += sy;
             z += sz;
-            if (x >= ext[0]) {
-                x -= ext[0];
+            if (x >= nch) {
+                x -= nch;
                 ++y;
             }
             if (y >= ext[1]) {
@@ -951,13 +1008,13 @@ __global__ __launch_bounds__(BLOCK) void k_grid_det_staged(GridView g, const flo
         if (ok && !taps) {   // empty space
             acc = det_background<KIND>(g, w);
         } else if (ok) {
+            const int row0 = ((base[2] - lo[2]) * ext[1] + (base[1] - lo[1])) * (4 * nch) + (base[0] - x0);
 #pragma unroll
             for (int cz = 0; cz < NT; ++cz) {
                 float plane = 0.0f;
 #pragma unroll
                 for (int cy = 0; cy < NT; ++cy) {
-                    const float* r = tile + ((base[2] + cz - lo[2]) * ext[1] + (base[1] + cy - lo[1])) * ext[0] +
-                                     (base[0] - lo[0]);
+                    const float* r = tile + row0 + (cz * ext[1] + cy) * (4 * nch);
                     float row = 0.0f;
 #pragma unroll
                     for (int cx = 0; cx < NT; ++cx) row = __builtin_fmaf(w[0][cx], r[cx], row);
@@ -968,9 +1025,15 @@ __global__ __launch_bounds__(BLOCK) void k_grid_det_staged(GridView g, const flo
         }
         __builtin_nontemporal_store(ok ? det_unscale<KIND>(acc) : __builtin_nanf(""), out + ((order && scatter) ? order[i] : i));
     } else {
+        float sum = 0.0f;
+        if constexpr (STAGE_QUADS<FMT>)
+            sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, reinterpret_cast<DetSlot*>(tile) + wave * 64);
+        else if (taps)
+            sum = det_taps<FMT, KIND>(g, base, leaf, w);
         if (!live) return;
-        __builtin_nontemporal_store(ok ? det_unscale<KIND>(det_sum_global<FMT, KIND>(g, base, w))
-                                                    : __builtin_nanf(""), out + ((order && scatter) ? order[i] : i));
+        if (!taps) sum = det_background<KIND>(g, w);
+        __builtin_nontemporal_store(ok ? det_unscale<KIND>(sum) : __builtin_nanf(""),
+                                    out + ((order && scatter) ? order[i] : i));
     }
 }
 
@@ -1060,15 +1123,13 @@ void launch3d_kind(const GridView& g, const float* q, int32_t n, int mode, uint3
         }
     } else {
         dim3 grid((n + BLOCK - 1) / BLOCK);
-        if (order && KIND != KIND_LINEAR)   // a sorted stream: neighbouring queries share their 64 taps
+        if constexpr (KIND == KIND_LINEAR)
+            hipLaunchKernelGGL((k_grid_det_linear<FMT>), grid, block, 0, stream, g, q, n, out, order, scatter);
+        else if (order)   // a sorted stream: neighbouring queries share their 64 taps
             hipLaunchKernelGGL((k_grid_det_staged<FMT, KIND>), grid, block, 0, stream, g, q, n, out, order, scatter,
                                stage_counters());
         else
-            if constexpr (KIND == KIND_LINEAR)
-                hipLaunchKernelGGL((k_grid_det_linear<FMT>), grid, block, 0, stream, g, q, n, out, order, scatter);
-            else
-                hipLaunchKernelGGL((k_grid_deterministic<FMT, KIND>), grid, block, 0, stream, g, q, n, out, order,
-                                   scatter);
+            hipLaunchKernelGGL((k_grid_deterministic<FMT, KIND>), grid, block, 0, stream, g, q, n, out, order, scatter);
     }
 }
 
