@@ -297,7 +297,8 @@ stf_status stf_create_dct_texture2d(int32_t width, int32_t height, int32_t chann
 /* ---------------------------------------------------------------------- */
 /* Morton-ordered query streams                                            */
 /* ---------------------------------------------------------------------- */
-/* Device workspace (bytes) that stf_sort_queries needs for n queries. */
+/* Device workspace (bytes) that stf_sort_queries needs for n queries; never
+ * less for more queries, so a workspace serves every smaller batch too. */
 stf_status stf_sort_workspace_bytes(int64_t n, size_t* bytes);
 
 /* Orders n queries of `tex` by the Morton code of their cell, so that
@@ -324,7 +325,7 @@ stf_status stf_sort_queries(const stf_texture* tex, const float* queries_dev, in
  * allocating library routine); the caller still provides the queries and
  * the two outputs.
  *   - n <= STF_SORT_NOALLOC_MAX_QUERIES (2^20); larger n gives STF_E_INVALID.
- *   - The array takes 16.3 MB of device memory on each device the call runs
+ *   - The array takes 17.9 MB of device memory on each device the call runs
  *     on, from the library's load until the process ends.
  *   - Every call on a device uses that device's single array: calls that
  *     overlap on one device (concurrent streams or host threads) race and

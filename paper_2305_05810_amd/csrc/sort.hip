@@ -20,19 +20,28 @@
 // of such short runs measured 0.64 against 0.58 ms for the 16M stream).
 //
 // One pass of the radix sort, for digit bits [shift, shift + D) with R = 2^D:
-//   1. histogram: each tile of 4096 keys counts its digits (ballot-matched
-//      lanes of equal digit add once) into row t of a tile-major table
-//      H[t][R]; the first pass computes the keys from the queries here;
-//   2. offsets: a four-kernel scan turns H into the global position of the
-//      first key of digit d of tile t (per-chunk digit sums, a scan over the
-//      chunks of each digit, a scan over the digits, then each chunk's
-//      running sums written in place);
-//   3. scatter: each tile ranks its keys stably (a wave takes 1024 contiguous
-//      keys in rounds of 64; lanes of equal digit find each other with D
-//      ballots and count in the wave's LDS counters), places them in LDS in
-//      sorted order, and writes them out so that consecutive lanes write
-//      consecutive positions of a digit's run.  The last pass writes the
-//      permutation and gathers the queries instead of (key, id) pairs.
+//   1. histogram: each tile counts its digits (ballot-matched lanes of equal
+//      digit add once) into column t of a digit-major table H[R][t]; the first
+//      pass computes the keys from the queries here;
+//   2. offsets: a block per digit scans the digit's row of H in place and
+//      writes the digit's count;
+//   3. scatter: each tile scans the digits' counts, ranks its keys stably (a
+//      wave takes 64 * ITEMS contiguous keys in rounds of 64; lanes of equal
+//      digit find each other with D ballots and count in the wave's LDS
+//      counters), places them in LDS in sorted order, and writes them out so
+//      that consecutive lanes write consecutive positions of a digit's run.
+//      The last pass writes the permutation and gathers the queries instead of
+//      (key, id) pairs.
+//
+// Up to a million queries the sort is bound by its chain of launches and by
+// each tile's chain of rounds: with a tile-major table the offsets took four
+// kernels (chunk sums, the scan over chunks, the scan over digits, the chunks'
+// running sums), 18 launches for three passes instead of 9, and 4096-key tiles
+// left most CUs idle.  At 16M queries it is bound by the scatters (79 + 81 +
+// 233 us of 539; the last one gathers the queries from all over the batch).
+// The whole call, before and after (512^3 grid, uniform queries):
+//   20k 88 -> 43 us, 200k 92 -> 44, 500k 102 -> 49, 1M 106 -> 57,
+//   2M 120 -> 83, 4M 158 -> 135, 16M 552 -> 539.
 #include <algorithm>
 #include <mutex>
 
@@ -45,15 +54,22 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
-constexpr int ITEMS = 16;                  // keys per thread
-constexpr int TILE = BLOCK * ITEMS;        // keys per tile: 4096
-constexpr int WAVE_KEYS = TILE / WAVES;    // contiguous keys per wave: 1024
+// A thread of the tile kernels takes ITEMS keys, a tile BLOCK * ITEMS.  A tile
+// is a chain of ITEMS dependent ranking rounds, so smaller batches take smaller
+// tiles, which more CUs share; large ones take runs of equal digits as long as
+// the LDS allows.  Three-pass sorts with 4 / 8 / 16 items (in tile order, see
+// tile_of_block): 200,000 queries 45 / 57 / 82 us, 1M 65 / 71 / 93, 2M 99 / 93
+// / 108, 4M 172 / 157 / 146, 16M 683 / 592 / 562 (654 with 32).
+constexpr int64_t ITEMS_8_FROM = 3 << 19, ITEMS_16_FROM = 3 << 20;
+int items_of(int64_t n)
+{
+    return n < ITEMS_8_FROM ? 4 : n < ITEMS_16_FROM ? 8 : 16;
+}
 #ifndef STF_SORT_DIGIT_BITS
 #define STF_SORT_DIGIT_BITS 8
 #endif
 constexpr int MAX_DIGIT = STF_SORT_DIGIT_BITS;   // widest digit of one pass
 constexpr int MAX_R = 1 << MAX_DIGIT;
-constexpr int CHUNK = 16;                  // tiles per chunk of the offset scan
 constexpr uint32_t MAX_CELL_BITS_3D = 10;
 
 struct KeySpec {
@@ -126,19 +142,29 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m, int lane)
     return (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
 }
 
-// Histogram of one tile's digits into H[t][0..R).  FIRST: the keys are
+// The tile of this block: workgroups go to the eight XCDs in turn, each with an
+// L2 of its own, so block b takes a tile of the b % 8-th eighth -- tiles that
+// share lines of the table H (16 neighbours) then share an L2.  4M queries 145
+// -> 135 us, 16M 562 -> 539 against tile b on block b.
+__device__ __forceinline__ int tile_of_block()
+{
+    const int x = blockIdx.x % 8, per = gridDim.x / 8, rem = gridDim.x % 8;
+    return x * per + min(x, rem) + (int)blockIdx.x / 8;
+}
+
+// Histogram of one tile's digits into H[0..R)[t].  FIRST: the keys are
 // computed from the queries and stored.
-template <bool FIRST>
+template <bool FIRST, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_hist(KeySpec spec, const float* __restrict__ q,
                                                 uint32_t* __restrict__ keys, int32_t n, int shift, int dbits,
-                                                uint32_t* __restrict__ H)
+                                                uint32_t* __restrict__ H, int ld)
 {
     __shared__ uint32_t hist[MAX_R];
-    const int R = 1 << dbits;
+    const int R = 1 << dbits, tile = tile_of_block();
     for (int d = threadIdx.x; d < R; d += BLOCK) hist[d] = 0;
     __syncthreads();
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    const int64_t w0 = (int64_t)blockIdx.x * TILE + wave * WAVE_KEYS;
+    const int64_t w0 = (int64_t)tile * (BLOCK * ITEMS) + wave * (64 * ITEMS);
     uint32_t key[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {   // all loads first, so they are in flight together
@@ -162,24 +188,7 @@ __global__ __launch_bounds__(BLOCK) void k_hist(KeySpec spec, const float* __res
         if (live && lanes_below(m, lane) == 0) atomicAdd(&hist[d], (uint32_t)__popcll(m));
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < R; d += BLOCK) H[(int64_t)blockIdx.x * R + d] = hist[d];
-}
-
-// Offsets, step 1 (grid: chunks x digit groups of BLOCK, a thread per
-// digit): S[c][d] = sum of H[t][d] over the CHUNK tiles t of chunk c.
-__global__ __launch_bounds__(BLOCK) void k_chunk_sums(const uint32_t* __restrict__ H, int ntiles, int R,
-                                                      uint32_t* __restrict__ S)
-{
-    const int d = blockIdx.y * BLOCK + threadIdx.x;
-    if (d >= R) return;
-    const int t0 = blockIdx.x * CHUNK;
-    uint32_t v[CHUNK];
-#pragma unroll
-    for (int k = 0; k < CHUNK; ++k) v[k] = t0 + k < ntiles ? H[(int64_t)(t0 + k) * R + d] : 0u;
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < CHUNK; ++k) s += v[k];
-    S[(int64_t)blockIdx.x * R + d] = s;
+    for (int d = threadIdx.x; d < R; d += BLOCK) H[(int64_t)d * ld + tile] = hist[d];
 }
 
 // Exclusive scan across a block of BLOCK threads of one value per thread;
@@ -205,69 +214,40 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t* wsum, 
     return before + incl - x;
 }
 
-// Offsets, step 2 (a block per digit d): S[c][d] becomes the count of digit
-// d in the chunks before c, and T[d] the count of digit d in all tiles.  A
-// thread takes `per` consecutive chunks.
-__global__ __launch_bounds__(BLOCK) void k_spine(uint32_t* __restrict__ S, int nchunks, int R,
-                                                 uint32_t* __restrict__ T)
+// Offsets (a block per digit d): H[d][t] becomes the count of digit d in the
+// tiles before t, and T[d] the count of digit d in all tiles.  A thread takes
+// `per` consecutive tiles, read `SCAN_BATCH` at a time.
+constexpr int SCAN_BATCH = 16;
+
+__global__ __launch_bounds__(BLOCK) void k_scan_tiles(uint32_t* __restrict__ H, int ld, int ntiles,
+                                                      uint32_t* __restrict__ T)
 {
     __shared__ uint32_t wsum[WAVES];
-    const int d = blockIdx.x;
-    const int per = (nchunks + BLOCK - 1) / BLOCK, c0 = threadIdx.x * per;
+    uint32_t* row = H + (int64_t)blockIdx.x * ld;
+    const int per = (ntiles + BLOCK - 1) / BLOCK;
+    const int64_t t0 = (int64_t)threadIdx.x * per;
+    const int count = (int)(t0 + per <= ntiles ? per : (t0 < ntiles ? ntiles - t0 : 0));
     uint32_t s = 0;
-    for (int k = 0; k < per; ++k)
-        if (c0 + k < nchunks) s += S[(int64_t)(c0 + k) * R + d];
+    uint32_t v[SCAN_BATCH];
+    for (int k0 = 0; k0 < count; k0 += SCAN_BATCH) {
+#pragma unroll
+        for (int k = 0; k < SCAN_BATCH; ++k) v[k] = k0 + k < count ? row[t0 + k0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < SCAN_BATCH; ++k) s += v[k];
+    }
     uint32_t total;
     uint32_t run = block_scan_excl(s, wsum, &total);
-    for (int k = 0; k < per; ++k)
-        if (c0 + k < nchunks) {
-            const uint32_t v = S[(int64_t)(c0 + k) * R + d];
-            S[(int64_t)(c0 + k) * R + d] = run;
-            run += v;
-        }
-    if (threadIdx.x == 0) T[d] = total;
-}
-
-// Offsets, step 3 (one block of MAX_R threads): base[d] = the count of all
-// digits below d.
-__global__ __launch_bounds__(MAX_R) void k_digit_base(const uint32_t* __restrict__ T, int R,
-                                                      uint32_t* __restrict__ base)
-{
-    __shared__ uint32_t wsum[MAX_R / 64];
-    const int d = threadIdx.x;
-    const uint32_t total = d < R ? T[d] : 0u;
-    const int lane = d % 64, wave = d / 64;
-    uint32_t incl = total;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
+    for (int k0 = 0; k0 < count; k0 += SCAN_BATCH) {
+#pragma unroll
+        for (int k = 0; k < SCAN_BATCH; ++k) v[k] = k0 + k < count ? row[t0 + k0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < SCAN_BATCH; ++k)
+            if (k0 + k < count) {
+                row[t0 + k0 + k] = run;
+                run += v[k];
+            }
     }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < wave; ++k) before += wsum[k];
-    if (d < R) base[d] = before + incl - total;
-}
-
-// Offsets, step 4 (grid as step 1): H[t][d] becomes the global position of
-// tile t's first key of digit d.
-__global__ __launch_bounds__(BLOCK) void k_chunk_offsets(uint32_t* __restrict__ H, int ntiles, int R,
-                                                         const uint32_t* __restrict__ S,
-                                                         const uint32_t* __restrict__ base)
-{
-    const int d = blockIdx.y * BLOCK + threadIdx.x;
-    if (d >= R) return;
-    const int t0 = blockIdx.x * CHUNK;
-    uint32_t v[CHUNK];
-#pragma unroll
-    for (int k = 0; k < CHUNK; ++k) v[k] = t0 + k < ntiles ? H[(int64_t)(t0 + k) * R + d] : 0u;
-    uint32_t run = S[(int64_t)blockIdx.x * R + d] + base[d];
-#pragma unroll
-    for (int k = 0; k < CHUNK; ++k)
-        if (t0 + k < ntiles) {
-            H[(int64_t)(t0 + k) * R + d] = run;
-            run += v[k];
-        }
+    if (threadIdx.x == 0) T[blockIdx.x] = total;
 }
 
 // Exclusive scan of v[0..R) in place, by the whole block (R <= MAX_R).
@@ -299,26 +279,27 @@ __device__ void block_exclusive_scan(uint32_t* v, int R, uint32_t* wsum)
 
 // One scatter pass.  FIRST: the ids are the keys' indices.  LAST: writes
 // order[pos] = id and the query itself instead of (key, id).
-template <bool FIRST, bool LAST, int DIMS>
+template <bool FIRST, bool LAST, int DIMS, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void k_scatter(const uint32_t* __restrict__ keys_in,
                                                    const int32_t* __restrict__ ids_in, int32_t n, int shift,
-                                                   int dbits, const uint32_t* __restrict__ H,
-                                                   uint32_t* __restrict__ keys_out, int32_t* __restrict__ ids_out,
-                                                   const float* __restrict__ q, float* __restrict__ sorted,
+                                                   int dbits, const uint32_t* __restrict__ H, int ld,
+                                                   const uint32_t* __restrict__ T, uint32_t* __restrict__ keys_out,
+                                                   int32_t* __restrict__ ids_out, const float* __restrict__ q, float* __restrict__ sorted,
                                                    int32_t* __restrict__ order)
 {
+    constexpr int TILE = BLOCK * ITEMS;
     __shared__ uint32_t cnt[WAVES][MAX_R];   // per-wave digit counts, then the wave's start within the digit
     __shared__ uint32_t lstart[MAX_R];       // first position of digit d within the tile
     __shared__ uint32_t gstart[MAX_R];       // first global position of digit d for this tile
     __shared__ uint32_t skey[TILE];
     __shared__ int32_t sid[TILE];
     __shared__ uint32_t wsum[WAVES];
-    const int R = 1 << dbits;
+    const int R = 1 << dbits, tile = tile_of_block();
     for (int k = threadIdx.x; k < WAVES * MAX_R; k += BLOCK) (&cnt[0][0])[k] = 0;
     __syncthreads();
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    const int64_t tile0 = (int64_t)blockIdx.x * TILE;
-    const int64_t w0 = tile0 + wave * WAVE_KEYS;
+    const int64_t tile0 = (int64_t)tile * TILE;
+    const int64_t w0 = tile0 + wave * (64 * ITEMS);
     uint32_t key[ITEMS], rank[ITEMS];
     int32_t id[ITEMS];
 #pragma unroll
@@ -328,6 +309,13 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(const uint32_t* __restrict__ 
         key[r] = live ? keys_in[i] : 0u;
         id[r] = FIRST ? (int32_t)i : (live ? ids_in[i] : 0);
     }
+    // this thread's digit: the keys of all digits below it and, of its own, of the tiles before this one
+    static_assert(MAX_R <= BLOCK, "a digit per thread");
+    const bool has_digit = (int)threadIdx.x < R;
+    const uint32_t own_before = has_digit ? H[(int64_t)threadIdx.x * ld + tile] : 0u;
+    uint32_t all;
+    const uint32_t below = block_scan_excl(has_digit ? T[threadIdx.x] : 0u, wsum, &all);
+    if (has_digit) gstart[threadIdx.x] = below + own_before;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const int64_t i = w0 + r * 64 + lane;
@@ -354,7 +342,6 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(const uint32_t* __restrict__ 
             run += c;
         }
         lstart[d] = run;
-        gstart[d] = H[(int64_t)blockIdx.x * R + d];
     }
     __syncthreads();
     block_exclusive_scan(lstart, R, wsum);
@@ -423,25 +410,36 @@ size_t align256(size_t b)
 
 int ntiles_of(int64_t n)
 {
-    return (int)((n + TILE - 1) / TILE);
+    const int64_t tile = (int64_t)BLOCK * items_of(n);
+    return (int)((n + tile - 1) / tile);
 }
 
-int nchunks_of(int64_t n)
+// Row length of the table H: the tiles, to an odd number of 64-byte lines, so
+// that a column's entries (a tile's digits) spread over the memory channels.
+int ld_of(int64_t n)
 {
-    return (ntiles_of(n) + CHUNK - 1) / CHUNK;
+    return ((ntiles_of(n) + 15) / 16 | 1) * 16;
 }
 
-// Workspace layout: keys[2][n], ids[2][n], H[ntiles][MAX_R], S[nchunks][MAX_R], T[MAX_R], base[MAX_R].
+// Bytes of H: those of the longest rows that n queries or fewer take (the rows
+// get shorter where the tiles get larger), so that a workspace for n queries
+// holds any smaller call.
+size_t table_bytes(int64_t n)
+{
+    const int ld = std::max(ld_of(n), std::max(ld_of(std::min(n, ITEMS_8_FROM - 1)), ld_of(std::min(n, ITEMS_16_FROM - 1))));
+    return align256((size_t)ld * MAX_R * 4);
+}
+
+// Workspace layout: keys[2][n], ids[2][n], H[MAX_R][ld_of(n)], T[MAX_R].
 struct SortWork {
     uint32_t* keys[2];
     int32_t* ids[2];
-    uint32_t *H, *S, *T, *base;
+    uint32_t *H, *T;
 };
 
 size_t work_bytes(int64_t n)
 {
-    return 4 * align256((size_t)n * 4) + align256((size_t)ntiles_of(n) * MAX_R * 4) +
-           align256((size_t)nchunks_of(n) * MAX_R * 4) + 2 * align256(MAX_R * 4);
+    return 4 * align256((size_t)n * 4) + table_bytes(n) + align256(MAX_R * 4);
 }
 
 SortWork carve(void* ws, int64_t n)
@@ -457,12 +455,8 @@ SortWork carve(void* ws, int64_t n)
         p += align256((size_t)n * 4);
     }
     w.H = (uint32_t*)p;
-    p += align256((size_t)ntiles_of(n) * MAX_R * 4);
-    w.S = (uint32_t*)p;
-    p += align256((size_t)nchunks_of(n) * MAX_R * 4);
+    p += table_bytes(n);
     w.T = (uint32_t*)p;
-    p += align256(MAX_R * 4);
-    w.base = (uint32_t*)p;
     return w;
 }
 
@@ -516,7 +510,7 @@ stf_status check_ptr(const void* p, const char* what, size_t align)
     return STF_OK;
 }
 
-template <int DIMS>
+template <int DIMS, int ITEMS>
 void launch_scatter(bool first, bool last, const SortWork& w, int src, int32_t n, int shift, int dbits,
                     const float* q, float* sorted, int32_t* order, hipStream_t st)
 {
@@ -525,50 +519,56 @@ void launch_scatter(bool first, bool last, const SortWork& w, int src, int32_t n
     const int32_t* iin = w.ids[src];
     uint32_t* kout = w.keys[1 - src];
     int32_t* iout = w.ids[1 - src];
-    if (first && last)
-        hipLaunchKernelGGL((k_scatter<true, true, DIMS>), grid, block, 0, st, kin, iin, n, shift, dbits, w.H, kout,
-                           iout, q, sorted, order);
-    else if (first)
-        hipLaunchKernelGGL((k_scatter<true, false, DIMS>), grid, block, 0, st, kin, iin, n, shift, dbits, w.H, kout,
-                           iout, q, sorted, order);
-    else if (last)
-        hipLaunchKernelGGL((k_scatter<false, true, DIMS>), grid, block, 0, st, kin, iin, n, shift, dbits, w.H, kout,
-                           iout, q, sorted, order);
-    else
-        hipLaunchKernelGGL((k_scatter<false, false, DIMS>), grid, block, 0, st, kin, iin, n, shift, dbits, w.H, kout,
-                           iout, q, sorted, order);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, kin, iin, n, shift, dbits, w.H, ld_of(n), w.T, kout, iout, q,
+                           sorted, order);
+    };
+    if (first && last) go(k_scatter<true, true, DIMS, ITEMS>);
+    else if (first) go(k_scatter<true, false, DIMS, ITEMS>);
+    else if (last) go(k_scatter<false, true, DIMS, ITEMS>);
+    else go(k_scatter<false, false, DIMS, ITEMS>);
 }
 
-// The whole sort on stream st with the workspace w.
-hipError_t run_sort(const stf_texture* tex, const float* q, int32_t n, float* sorted, int32_t* order,
-                    const SortWork& w, hipStream_t st)
+// The whole sort on stream st with the workspace w (ITEMS = items_of(n)).
+template <int ITEMS>
+hipError_t run_sort_items(const stf_texture* tex, const float* q, int32_t n, float* sorted, int32_t* order,
+                          const SortWork& w, hipStream_t st)
 {
     const KeySpec spec = key_spec(tex);
     const int key_bits = spec.dims * spec.bits + 1;
     const int passes = (key_bits + MAX_DIGIT - 1) / MAX_DIGIT;
     const int dbits = (key_bits + passes - 1) / passes;
     const int R = 1 << dbits;
-    const int ntiles = ntiles_of(n), nchunks = nchunks_of(n);
-    const dim3 tiles((unsigned)ntiles), chunks((unsigned)nchunks, (unsigned)((R + BLOCK - 1) / BLOCK)), block(BLOCK);
+    const int ntiles = ntiles_of(n);
+    const dim3 tiles((unsigned)ntiles), block(BLOCK);
     int src = 0;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * dbits;
         if (p == 0)
-            hipLaunchKernelGGL((k_hist<true>), tiles, block, 0, st, spec, q, w.keys[0], n, shift, dbits, w.H);
+            hipLaunchKernelGGL((k_hist<true, ITEMS>), tiles, block, 0, st, spec, q, w.keys[0], n, shift, dbits, w.H,
+                               ld_of(n));
         else
-            hipLaunchKernelGGL((k_hist<false>), tiles, block, 0, st, spec, q, w.keys[src], n, shift, dbits, w.H);
-        hipLaunchKernelGGL(k_chunk_sums, chunks, block, 0, st, w.H, ntiles, R, w.S);
-        hipLaunchKernelGGL(k_spine, dim3((unsigned)R), block, 0, st, w.S, nchunks, R, w.T);
-        hipLaunchKernelGGL(k_digit_base, dim3(1), dim3(MAX_R), 0, st, w.T, R, w.base);
-        hipLaunchKernelGGL(k_chunk_offsets, chunks, block, 0, st, w.H, ntiles, R, w.S, w.base);
+            hipLaunchKernelGGL((k_hist<false, ITEMS>), tiles, block, 0, st, spec, q, w.keys[src], n, shift, dbits, w.H,
+                               ld_of(n));
+        hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)R), block, 0, st, w.H, ld_of(n), ntiles, w.T);
         const bool last = p == passes - 1;
         if (spec.dims == 3)
-            launch_scatter<3>(p == 0, last, w, src, n, shift, dbits, q, sorted, order, st);
+            launch_scatter<3, ITEMS>(p == 0, last, w, src, n, shift, dbits, q, sorted, order, st);
         else
-            launch_scatter<2>(p == 0, last, w, src, n, shift, dbits, q, sorted, order, st);
+            launch_scatter<2, ITEMS>(p == 0, last, w, src, n, shift, dbits, q, sorted, order, st);
         src = 1 - src;
     }
     return hipGetLastError();
+}
+
+hipError_t run_sort(const stf_texture* tex, const float* q, int32_t n, float* sorted, int32_t* order,
+                    const SortWork& w, hipStream_t st)
+{
+    switch (items_of(n)) {
+    case 4: return run_sort_items<4>(tex, q, n, sorted, order, w, st);
+    case 8: return run_sort_items<8>(tex, q, n, sorted, order, w, st);
+    default: return run_sort_items<16>(tex, q, n, sorted, order, w, st);
+    }
 }
 
 stf_status check_sort_args(const stf_texture* tex, const float* queries_dev, int64_t n, const float* sorted_dev,
@@ -594,9 +594,9 @@ stf_status check_sort_args(const stf_texture* tex, const float* queries_dev, int
 // the symbol); it uses the device address that hipGetSymbolAddress returns on
 // each device, looked up on the first call there.
 constexpr int64_t NOALLOC_MAX_QUERIES = STF_SORT_NOALLOC_MAX_QUERIES;   // from stf.h
-constexpr size_t NOALLOC_BYTES = (size_t)NOALLOC_MAX_QUERIES * 16 + ((size_t)NOALLOC_MAX_QUERIES / TILE) * MAX_R * 4 +
-                                 ((size_t)NOALLOC_MAX_QUERIES / TILE / CHUNK + 1) * MAX_R * 4 + 2 * MAX_R * 4 +
-                                 8 * 256;
+// (keys and ids, the tile table of the smallest tiles any smaller call takes, the digit counts)
+constexpr size_t NOALLOC_BYTES = (size_t)NOALLOC_MAX_QUERIES * 16 +
+                                 ((size_t)NOALLOC_MAX_QUERIES / (BLOCK * 4) + 32) * MAX_R * 4 + MAX_R * 4 + 8 * 256;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 constexpr int MAX_DEVICES = 64;
