@@ -25,7 +25,8 @@
 // the hidden units are stored in the order the accumulator layout produces.
 // A wave runs two batches at a time: each of its 64 lanes does the tap
 // choice, latent gather and interpolation of one of the 64 decodes, and a
-// lane-half swap forms both batches' first B operands.
+// lane-half swap forms both batches' first B operands.  The 8 output channels
+// use products of 16 columns.
 #include <math.h>
 #include <string.h>
 
@@ -513,17 +514,17 @@ __global__ void k_to_quads(const float* __restrict__ lat, uint16_t* __restrict__
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Operand images: one 8-value A slot per lane for every MFMA.  Biases enter
-// the products themselves: every bias is split exactly into three bf16 terms
-// held in k-slots 8..10 of an A operand, which meet ones in the same slots of
-// the B operand.  Layer 1 uses its padding slots for this; layers 2 and 3
-// start their accumulation with one bias-only MFMA.
+// Operand images: one 8-value A slot per lane for every MFMA.  Layer 1's
+// biases enter in its padding slots: each is split exactly into three bf16
+// terms held in k-slots 8..10 of the A operand, which meet ones in the same
+// slots of the B operand.  Layers 2 and 3 start their accumulation from the
+// biases themselves, held in the accumulator's layout.
 struct Packed {
     bf16x8 a1[2][64];      // layer 1, M-blocks of 32 hidden units; k 0..7 latent, 8..10 bias terms
     bf16x8 a2[2][4][64];   // layer 2, M-blocks x K-blocks of 16
-    bf16x8 a3[4][64];      // layer 3, rows 0..7 real, 8..31 zero
-    bf16x8 ab2[2][64];     // layer 2 bias terms per M-block
-    bf16x8 ab3[64];        // layer 3 bias terms
+    bf16x8 a3[2][64];      // layer 3, K-blocks of 32; rows 0..7 the channels, 8..15 the same again
+    f32x16 b2[2][2];       // layer 2 biases per lane half and M-block
+    f32x4 b3[2];           // layer 3 biases of channels 0..3 and 4..7
 };
 
 // Hidden unit held by k-slot kappa = 16 kb + 8 h + j of the B operand when
@@ -538,8 +539,14 @@ __host__ __device__ constexpr int row_of_acc(int mb, int h, int r)
 {
     return 32 * mb + 8 * (r / 4) + 4 * h + (r % 4);
 }
-static_assert(row_of_acc(0, 0, 0) == 0 && row_of_acc(0, 1, 3) == 7,
-              "registers 0..3 of lane half h hold output channels 4h..4h+3");
+
+// Hidden unit met by slot j of lane group g (of 16 lanes) in layer 3's K-block
+// kb2 of 32: layer_3 swaps the odd groups of the even K-block of 16 with the
+// even groups of the odd one.
+__host__ __device__ constexpr int hidden_of_slot3(int kb2, int g, int j)
+{
+    return hidden_of_slot(2 * kb2 + g % 2, g / 2, j);
+}
 
 struct InferArgs {
     const Packed* pk;
@@ -582,6 +589,16 @@ struct Decode {
     bool fin;
 };
 
+// Six times the weight of one cubic B-spline tap, as cubic6 computes it: tap
+// is fixed per lane, so its cases are selects on lane masks.
+__device__ __forceinline__ float cubic6_tap(int tap, float t)
+{
+    const bool inner = tap == 1 || tap == 2;
+    const float s = 1.0f - t, u = tap < 2 ? s : t;
+    const float p = (inner ? 3.0f : u) * u, q = inner ? 1.0f + s * t : u;
+    return (inner ? 1.0f : 0.0f) + p * q;
+}
+
 template <bool CUBIC, bool STOCH>
 __device__ __forceinline__ Decode locate(const InferArgs& a, uint32_t qi, int tap, float2 uv)
 {
@@ -589,7 +606,9 @@ __device__ __forceinline__ Decode locate(const InferArgs& a, uint32_t qi, int ta
     float x = uv.x * (float)a.W - 0.5f, y = uv.y * (float)a.H - 0.5f;
     int cx = 0, cy = 0;
     float tx = 0.0f, ty = 0.0f;
-    d.fin = cell_of(x, cx, tx) & cell_of(y, cy, ty);
+    d.fin = (__builtin_fabsf(x) < TWO24) & (__builtin_fabsf(y) < TWO24);
+    (void)cell_of(d.fin ? x : 0.0f, cx, tx);
+    (void)cell_of(d.fin ? y : 0.0f, cy, ty);
     d.w = 1.0f;
     if constexpr (STOCH) {
         const uint32_t base = pcg_base(pcg(a.key ^ qi));
@@ -601,14 +620,6 @@ __device__ __forceinline__ Decode locate(const InferArgs& a, uint32_t qi, int ta
             d.sx = cx + choose_linear_m(tx, mx);
             d.sy = cy + choose_linear_m(ty, my);
         }
-    } else if constexpr (CUBIC) {
-        int ta = tap % 4, tb = tap / 4;
-        Cubic6 wa = cubic6(tx), wb = cubic6(ty);
-        float fa = ta == 0 ? wa.a0 : ta == 1 ? wa.a1 : ta == 2 ? wa.a2 : wa.a3;
-        float fb = tb == 0 ? wb.a0 : tb == 1 ? wb.a1 : tb == 2 ? wb.a2 : wb.a3;
-        d.w = (fa * K6) * (fb * K6);
-        d.sx = cx - 1 + ta;
-        d.sy = cy - 1 + tb;
     } else {
         int ta = tap % 2, tb = tap / 2;
         d.w = (ta ? tx : 1.0f - tx) * (tb ? ty : 1.0f - ty);
@@ -620,28 +631,83 @@ __device__ __forceinline__ Decode locate(const InferArgs& a, uint32_t qi, int ta
     return d;
 }
 
-// The corner quad of a decode's texel (its four clamped latent corners,
-// 64 contiguous bytes: one cache line) and their bilinear weights.  With
-// LW <= W the cell x0 = floor(X) lies in -1 .. LW - 1 (likewise y0).
-__device__ __forceinline__ uint32_t latent_quad(const InferArgs& a, const Decode& d, float (&w)[4])
+// The latent cell of texel s on one axis (ratio = L / size): the index of its
+// lower corner plus one, and the fraction.  With L <= size the corner
+// floor(X) lies in -1 .. L - 1.
+__device__ __forceinline__ int latent_cell(int s, float ratio, int L, float& f)
 {
-    float X = ((float)d.sx + 0.5f) * a.rx - 0.5f, Y = ((float)d.sy + 0.5f) * a.ry - 0.5f;
-    float fx0 = floorf(X), fy0 = floorf(Y);
-    float fx = X - fx0, fy = Y - fy0;
-    const int x0 = min(max((int)fx0, -1), a.LW - 1), y0 = min(max((int)fy0, -1), a.LH - 1);
+    const float X = ((float)s + 0.5f) * ratio - 0.5f, x0 = floorf(X);
+    f = X - x0;
+    return min(max((int)x0, -1), L - 1) + 1;
+}
+
+// The corner quad of latent cell (i, j) (its four clamped latent corners,
+// 64 contiguous bytes: one cache line) and their bilinear weights.
+__device__ __forceinline__ uint32_t latent_quad(const InferArgs& a, int i, int j, float fx, float fy, float (&w)[4])
+{
     w[0] = (1.0f - fx) * (1.0f - fy);
     w[1] = fx * (1.0f - fy);
     w[2] = (1.0f - fx) * fy;
     w[3] = fx * fy;
-    return (uint32_t)((y0 + 1) * (a.LW + 1) + (x0 + 1));   // below 2^27 quads
+    return __umul24((uint32_t)j, (uint32_t)(a.LW + 1)) + (uint32_t)i;   // sides to 65537, below 2^27 quads
+}
+
+// One axis of a cubic tap: its weight (NaN for a non-finite coordinate) and
+// the latent cell and fraction of its texel.
+struct AxisTap {
+    float w, f;
+    int i;
+};
+
+__device__ __forceinline__ AxisTap locate_axis(float u, int size, int L, float ratio, int tap)
+{
+    const float x = u * (float)size - 0.5f;
+    const bool fin = __builtin_fabsf(x) < TWO24;
+    int c = 0;
+    float t = 0.0f;
+    (void)cell_of(fin ? x : 0.0f, c, t);
+    AxisTap d;
+    d.w = fin ? cubic6_tap(tap, t) * K6 : __builtin_nanf("");
+    d.i = latent_cell(clampi(c - 1 + tap, size - 1), ratio, L, d.f);
+    return d;
+}
+
+// Layer 3 on a 32-decode batch: the 8 output rows would fill a quarter of a
+// 32 x 32 product, so the decodes are split into two blocks of 16 columns
+// instead (half the matrix cycles).  Swapping the odd rows of 16 lanes of one
+// hidden K-block with the even rows of the next turns two B operands of the
+// 32-column layout into one of each block.  The weights' rows 8..15 repeat the
+// channels, so that lane groups 0, 1 take the first block's results and groups
+// 2, 3 the second's: lane l ends with channels 4 (l / 16 % 2) .. + 3 of decode
+// 16 (l / 32) + l % 16.
+__device__ __forceinline__ f32x4 layer_3(const bf16x8 (&B3)[4], const bf16x8 (&A3)[2], const f32x4& C3, bool upper)
+{
+    f32x4 D[2] = {C3, C3};
+#pragma unroll
+    for (int kb2 = 0; kb2 < 2; ++kb2) {
+        const uint4 x = __builtin_bit_cast(uint4, B3[2 * kb2]), y = __builtin_bit_cast(uint4, B3[2 * kb2 + 1]);
+        const auto r0 = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+        const auto r1 = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+        const auto r2 = __builtin_amdgcn_permlane16_swap(x.z, y.z, false, false);
+        const auto r3 = __builtin_amdgcn_permlane16_swap(x.w, y.w, false, false);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            const bf16x8 B = __builtin_bit_cast(bf16x8, make_uint4(r0[nb], r1[nb], r2[nb], r3[nb]));
+            D[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A3[kb2], B, D[nb], 0, 0, 0);
+        }
+    }
+    f32x4 o;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) o[c] = upper ? D[1][c] : D[0][c];
+    return o;
 }
 
 // The decoder MLP on one 32-decode batch: B1 holds the bf16 latents of the
 // batch's decodes in k-slots 0..7 (lanes 0..31) and ones in the bias slots
-// 8..10 (lanes 32..63).  Returns layer 3's accumulator.
-__device__ __forceinline__ f32x16 mlp_batch(const bf16x8& B1, const bf16x8 (&A1)[2], const bf16x8 (&A2)[2][4],
-                                            const bf16x8 (&A3)[4], const bf16x8 (&AB2)[2], const bf16x8& AB3,
-                                            const bf16x8& ONES)
+// 8..10 (lanes 32..63).  Returns four channels of one decode per lane (see
+// layer_3).
+__device__ __forceinline__ f32x4 mlp_batch(const bf16x8& B1, const bf16x8 (&A1)[2], const bf16x8 (&A2)[2][4],
+                                           const bf16x8 (&A3)[2], const f32x16* C2, const f32x4& C3, bool upper)
 {
     const f32x16 Z = {};
     // A wave in its matrix chain runs at raised issue priority, so the
@@ -656,11 +722,11 @@ __device__ __forceinline__ f32x16 mlp_batch(const bf16x8& B1, const bf16x8 (&A1)
     bf16x8 B2[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) B2[kb] = relu_bf16(D1[kb / 2], 8 * (kb % 2));
-    // layer 2: bias, then 64 x 64 by 64 x 32
+    // layer 2: bias + 64 x 64 by 64 x 32
     f32x16 D2[2];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
-        D2[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AB2[mb], ONES, Z, 0, 0, 0);
+        D2[mb] = C2[mb];
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
             D2[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2[mb][kb], B2[kb], D2[mb], 0, 0, 0);
@@ -668,12 +734,9 @@ __device__ __forceinline__ f32x16 mlp_batch(const bf16x8& B1, const bf16x8 (&A1)
     bf16x8 B3[4];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) B3[kb] = relu_bf16(D2[kb / 2], 8 * (kb % 2));
-    // layer 3: bias, then 8 (of 32) x 64 by 64 x 32
-    f32x16 D3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(AB3, ONES, Z, 0, 0, 0);
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) D3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A3[kb], B3[kb], D3, 0, 0, 0);
+    const f32x4 o = layer_3(B3, A3, C3, upper);
     __builtin_amdgcn_s_setprio(0);
-    return D3;
+    return o;
 }
 
 // Sum of v over each group of TAPS consecutive lanes (TAPS = 1, 4 or 16),
@@ -704,11 +767,11 @@ __device__ __forceinline__ float tap_sum(float v)
     return v;
 }
 
-// Registers 0..3 of layer 3's accumulator hold channels 4h..4h+3 of decode
-// jd; weight them, sum the taps of each query and store.  A non-finite query
-// carries a NaN weight, so every channel it stores is NaN.
+// Four channels of a decode per lane, weighted: sum the taps of each query and
+// store.  A non-finite query carries a NaN weight, so every channel it stores
+// is NaN.
 template <int TAPS>
-__device__ __forceinline__ void emit(const InferArgs& a, const f32x16& D3, float w, uint32_t qi, int tap, int h)
+__device__ __forceinline__ void emit(const InferArgs& a, const f32x4& D3, float w, uint32_t qi, int tap, int cg)
 {
     float o[4] = {D3[0] * w, D3[1] * w, D3[2] * w, D3[3] * w};
 #pragma unroll
@@ -716,72 +779,101 @@ __device__ __forceinline__ void emit(const InferArgs& a, const f32x16& D3, float
     typedef float f32x4_nt __attribute__((ext_vector_type(4)));   // results are streamed out
     if (qi < (uint32_t)a.n && tap == 0)
         __builtin_nontemporal_store((f32x4_nt){o[0], o[1], o[2], o[3]},
-                                    reinterpret_cast<f32x4_nt*>(a.out) + (2 * (size_t)qi + h));
+                                    reinterpret_cast<f32x4_nt*>(a.out) + (2 * (size_t)qi + cg));
 }
 
-// Persistent waves; each handles pairs of 32-decode batches p = wave,
-// wave + nwaves, ...  Lane l does the per-decode work (tap choice, latent
-// gather and interpolation) for decode l of the pair, so no lane repeats
-// another's; one cross-half swap then lays the two batches' latents out as
-// MFMA B operands, each with the bias ones in its upper half.  The loop is
-// software-pipelined: while pair i runs its MFMAs, the latents of pair i + 1
-// and the queries of pair i + 2 are in flight.
+// Lanes with `odd` keep b, the others a: each adds the partner's share of the
+// kept value, which CTRL (a swap of lanes that differ in `odd`) brings.
+template <int CTRL>
+__device__ __forceinline__ float keep_sum(float a, float b, bool odd)
+{
+    const float keep = odd ? b : a, give = odd ? a : b;
+    return keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give), CTRL, 0xF, 0xF, true));
+}
+
+// The 16-tap sums of both batches of a pair (a row of 16 lanes holds a query's
+// taps): the eight values a lane holds are halved at each step with the lanes
+// that share their sum, 14 additions instead of 32.  Lane l (of those with
+// l / 4 even) ends with channel 4 (l / 16 % 2) + l % 4 of query
+// 2 (l / 8 % 2) + l / 32 of the pair's four, 128 contiguous bytes per wave.
+__device__ __forceinline__ void emit16(const InferArgs& a, const f32x4 (&D3)[2], const float (&w)[2], uint32_t q0,
+                                       int lane)
+{
+    float v[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const float r0 = keep_sum<0xB1>(D3[b][0] * w[b], D3[b][1] * w[b], lane & 1);   // quad_perm [1,0,3,2]
+        const float r1 = keep_sum<0xB1>(D3[b][2] * w[b], D3[b][3] * w[b], lane & 1);
+        v[b] = keep_sum<0x4E>(r0, r1, lane & 2);                                       // quad_perm [2,3,0,1]
+    }
+    float r = keep_sum<0x128>(v[0], v[1], lane & 8);   // row_ror:8
+    r += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, r), 0x104, 0xF, 0xF, true));   // row_shl:4
+    const uint32_t qi = q0 + 2 * (lane / 8 % 2) + lane / 32;
+    if (qi < (uint32_t)a.n && (lane & 4) == 0)
+        __builtin_nontemporal_store(r, a.out + 8 * (size_t)qi + 4 * (lane / 16 % 2) + lane % 4);
+}
+
+// Persistent waves, each handling pairs of 32-decode batches: lane l does the
+// per-decode work (latent gather and interpolation) for decode l of the pair,
+// so no lane repeats another's; one cross-half swap then lays the two batches'
+// latents out as MFMA B operands, each with the bias ones in its upper half.
+//
+// The large calls run at the clock that the card's power leaves this mix, about
+// 1.75 GHz, with the VALU issuing in nine of ten cycles and the matrix cores
+// busy in half of them: time goes with the work, however it is interleaved (two
+// waves per SIMD with both batches' chains abreast, or no raised priority:
+// 890 and 907 us against 870).  What was taken out, for 4M queries of 16 taps
+// (948 us before, 870 after): layer 3 as two blocks of 16 columns, layer 2's
+// and 3's biases as accumulator starts (17 products of 32 x 32 x 16 per batch,
+// now 10 and 4 of half the cycles), each axis of a tap located once instead of
+// in every lane of the 4 x 4 block, one reduction for both batches' tap sums,
+// stages that swap without moves (390 VALU instructions per pair, now 320).
 template <bool CUBIC, bool STOCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_ntex_infer(InferArgs a)
 {
     constexpr int TAPS = STOCH ? 1 : (CUBIC ? 16 : 4);
     constexpr int QPB = 32 / TAPS;   // queries per 32-decode batch
     constexpr int QPP = 2 * QPB;     // queries per pair of batches
-    const int lane = threadIdx.x % 64, h = lane / 32, jd = lane % 32;
+    const int lane = threadIdx.x % 64, h = lane / 32;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / 64;
     const int nwaves = gridDim.x * blockDim.x / 64;
     const Packed* __restrict__ pk = a.pk;
-    bf16x8 A1[2], A2[2][4], A3[4], AB2[2], AB3, ONES;
+    bf16x8 A1[2], A2[2][4], A3[2];
+    // The biases of layers 2 and 3 are read where they are needed: held in
+    // registers for the whole loop they would not leave room for three waves.
+    __shared__ f32x16 C2s[2][2];
+    __shared__ f32x4 C3s[2];
+    if (threadIdx.x < 64) reinterpret_cast<float*>(C2s)[threadIdx.x] = reinterpret_cast<const float*>(pk->b2)[threadIdx.x];
+    if (threadIdx.x < NO) reinterpret_cast<float*>(C3s)[threadIdx.x] = reinterpret_cast<const float*>(pk->b3)[threadIdx.x];
+    __syncthreads();
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
         A1[mb] = pk->a1[mb][lane];
-        AB2[mb] = pk->ab2[mb][lane];
+        A3[mb] = pk->a3[mb][lane];
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) A2[mb][kb] = pk->a2[mb][kb][lane];
     }
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) A3[kb] = pk->a3[kb][lane];
-    AB3 = pk->ab3[lane];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ONES[j] = (__bf16)((h == 1 && j < 3) ? 1.0f : 0.0f);   // k-slots 8..10
     // The bias ones as every lane's slots j = 0..2 hold them in the upper
     // half: (1, 1, 1, 0, 0, 0, 0, 0) in bf16, as four 32-bit words.
     const uint32_t ONE_WORDS[4] = {0x3F803F80u, 0x00003F80u, 0u, 0u};
 
     const int32_t npair = (int32_t)(((int64_t)a.n + QPP - 1) / QPP);
     const uint32_t nq = (uint32_t)a.n;
-    const int tap = lane % TAPS;
     const uint4* L = reinterpret_cast<const uint4*>(a.quad16);
-    auto load_uv = [&](int32_t p) {
-        const uint32_t qi = (uint32_t)p * QPP + lane / TAPS;
-        return (p < npair && qi < nq) ? reinterpret_cast<const float2*>(a.q)[qi] : make_float2(0.5f, 0.5f);
-    };
-    // Every lane loads: the quad index is in the table for any query
-    // (padding lanes carry uv = (0.5, 0.5)).
-    auto load_lat = [&](const Decode& d, uint4 (&v)[4], float (&w)[4]) {
-        const uint32_t e = latent_quad(a, d, w);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = L[4 * (size_t)e + k];
-    };
 
-    int32_t p = wave;
-    float2 uv_next = load_uv(p + nwaves);
-    Decode cur = locate<CUBIC, STOCH>(a, (uint32_t)p * QPP + lane / TAPS, tap, load_uv(p));
-    uint4 lat_cur[4];
-    float wl_cur[4];
-    load_lat(cur, lat_cur, wl_cur);
-    for (; p < npair; p += nwaves) {
-        // ---- stage the next two pairs
-        const float2 uv_after = load_uv(p + 2 * nwaves);
-        const Decode nxt = locate<CUBIC, STOCH>(a, (uint32_t)(p + nwaves) * QPP + lane / TAPS, tap, uv_next);
-        uint4 lat_nxt[4];
-        float wl_nxt[4];
-        load_lat(nxt, lat_nxt, wl_nxt);
+    // A pair's decode of this lane, its latents in flight.  Every lane loads:
+    // the quad index is in the table for any query.
+    struct Stage {
+        float w, wl[4];   // tap weight, corner weights
+        uint4 lat[4];
+        int sx, sy;       // texel (stochastic)
+    };
+    auto load_lat = [&](Stage& st, int i, int j, float fx, float fy) {
+        const uint32_t e = latent_quad(a, i, j, fx, fy, st.wl);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) st.lat[k] = L[4 * (size_t)e + k];
+    };
+    auto one_pair = [&](int32_t p, const Stage& cur) {
         // ---- latent interpolation of this lane's decode, rounded to bf16
         uint32_t X[4];
 #pragma unroll
@@ -790,14 +882,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int sh = 16 * half;
-                const uint32_t* p0 = reinterpret_cast<const uint32_t*>(&lat_cur[0]);
-                const uint32_t* p1 = reinterpret_cast<const uint32_t*>(&lat_cur[1]);
-                const uint32_t* p2 = reinterpret_cast<const uint32_t*>(&lat_cur[2]);
-                const uint32_t* p3 = reinterpret_cast<const uint32_t*>(&lat_cur[3]);
-                float s = wl_cur[0] * dec_f16((uint16_t)(p0[wsel] >> sh));
-                s = __builtin_fmaf(wl_cur[1], dec_f16((uint16_t)(p1[wsel] >> sh)), s);
-                s = __builtin_fmaf(wl_cur[2], dec_f16((uint16_t)(p2[wsel] >> sh)), s);
-                s = __builtin_fmaf(wl_cur[3], dec_f16((uint16_t)(p3[wsel] >> sh)), s);
+                float s = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    s = __builtin_fmaf(cur.wl[k],
+                                       dec_f16((uint16_t)(reinterpret_cast<const uint32_t*>(&cur.lat[k])[wsel] >> sh)), s);
                 v[half] = s;
             }
             X[wsel] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){v[0], v[1]}, bf16x2));
@@ -812,32 +901,106 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             B1w[0][k] = r[0];
             B1w[1][k] = r[1];
         }
-        // decode weights in the same way: lane l of batch b needs decode 32 b + l % 32's
-        const float wd = cur.fin ? cur.w : __builtin_nanf("");
-        const uint32_t wb = __builtin_bit_cast(uint32_t, wd);
-        const auto rw = __builtin_amdgcn_permlane32_swap(wb, wb, false, false);
-        const uint32_t q0 = (uint32_t)p * QPP + jd / TAPS;
+        // decode weights to where layer 3 leaves the decodes: lane l of batch b
+        // needs that of decode 32 b + 16 (l / 32) + l % 16
+        const uint32_t wb = __builtin_bit_cast(uint32_t, cur.w);
+        const auto rows = __builtin_amdgcn_permlane16_swap(wb, wb, false, false);
+        const auto rw = __builtin_amdgcn_permlane32_swap(rows[0], rows[1], false, false);
+        const float w[2] = {__builtin_bit_cast(float, (uint32_t)rw[0]), __builtin_bit_cast(float, (uint32_t)rw[1])};
+        const uint32_t q0 = (uint32_t)p * QPP;
+        f32x4 D3[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const bf16x8 B1 = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(B1w[b]));
-            const f32x16 D3 = mlp_batch(B1, A1, A2, A3, AB2, AB3, ONES);
-            emit<TAPS>(a, D3, __builtin_bit_cast(float, (uint32_t)rw[b]), q0 + b * QPB, tap, h);
+            const bf16x8 B1 = __builtin_bit_cast(bf16x8, make_uint4(B1w[b][0], B1w[b][1], B1w[b][2], B1w[b][3]));
+            int at = lane / 16;   // not known to be the same in every turn
+            asm volatile("" : "+v"(at));
+            D3[b] = mlp_batch(B1, A1, A2, A3, C2s[at / 2], C3s[at % 2], h);
+            if constexpr (TAPS != 16)
+                emit<TAPS>(a, D3[b], w[b], q0 + b * QPB + (16 * h + lane % 16) / TAPS, lane % TAPS, lane / 16 % 2);
         }
+        if constexpr (TAPS == 16) emit16(a, D3, w, q0, lane);
         // selected texel of this lane's own decode (stochastic: one decode per query)
         if (STOCH && a.idx) {
-            const uint32_t qi = (uint32_t)p * QPP + lane;
+            const uint32_t qi = q0 + lane;
             if (qi < nq) {
-                a.idx[2 * (size_t)qi] = cur.fin ? cur.sx : BAD_INDEX;
-                a.idx[2 * (size_t)qi + 1] = cur.fin ? cur.sy : BAD_INDEX;
+                const bool fin = cur.w == cur.w;
+                a.idx[2 * (size_t)qi] = fin ? cur.sx : BAD_INDEX;
+                a.idx[2 * (size_t)qi + 1] = fin ? cur.sy : BAD_INDEX;
             }
         }
-        cur = nxt;
-        uv_next = uv_after;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            lat_cur[k] = lat_nxt[k];
-            wl_cur[k] = wl_nxt[k];
+    };
+
+    Stage S0, S1;
+    if constexpr (TAPS == 16) {
+        // Two neighbouring pairs a turn (one where there are waves for all):
+        // the 64 lanes locate the four taps of both axes of their eight
+        // queries, and each pair's decodes fetch their two axes from there.
+        // While a pair runs its MFMAs, the next one's latents are in flight,
+        // and a turn ahead the queries.
+        const int both = npair > nwaves ? 2 : 1;
+        const int axis = lane / 4 % 2;
+        const int from_x = 4 * (8 * (lane / 16) + lane % 4), from_y = 4 * (8 * (lane / 16) + 4 + lane / 4 % 4);
+        const int32_t nturn = (npair + both - 1) / both;
+        auto load_u = [&](int32_t t) {
+            const uint32_t qi = min((uint32_t)t * (both * QPP) + lane / 8, nq - 1);
+            return a.q[2 * (size_t)qi + axis];
+        };
+        auto fetch = [&](const AxisTap& ax, int second, Stage& st) {
+            auto from = [&](int at, int v) { return __builtin_amdgcn_ds_bpermute(at + 128 * second, v); };
+            auto fromf = [&](int at, float v) { return __builtin_bit_cast(float, from(at, __builtin_bit_cast(int, v))); };
+            st.w = fromf(from_x, ax.w) * fromf(from_y, ax.w);
+            load_lat(st, from(from_x, ax.i), from(from_y, ax.i), fromf(from_x, ax.f), fromf(from_y, ax.f));
+        };
+        auto locate_turn = [&](float u) {
+            int y = axis;   // selected anew in every turn: four registers fewer in the loop
+            asm volatile("" : "+v"(y));
+            return locate_axis(u, y ? a.H : a.W, y ? a.LH : a.LW, y ? a.ry : a.rx, lane % 4);
+        };
+        int32_t t = wave;
+        if (t >= nturn) return;
+        AxisTap ax = locate_turn(load_u(t));
+        float u_next = load_u(min(t + nwaves, nturn - 1));
+        fetch(ax, 0, S0);
+        for (;; t += nwaves) {
+            const int32_t p = t * both;
+            if (both == 2) fetch(ax, 1, S1);
+            one_pair(p, S0);
+            if (both == 1 || p + 1 >= npair) break;
+            ax = locate_turn(u_next);
+            u_next = load_u(min(t + 2 * nwaves, nturn - 1));
+            fetch(ax, 0, S0);
+            one_pair(p + 1, S1);
+            if (t + nwaves >= nturn) break;
         }
+    } else {
+        // While pair i runs its MFMAs, the latents of pair i + 1 and the
+        // queries of pair i + 2 are in flight; two pairs a turn, so that the
+        // stages swap without moves.
+        auto load_uv = [&](int32_t p) {   // past the end: the last query
+            return reinterpret_cast<const float2*>(a.q)[min((uint32_t)p * QPP + lane / TAPS, nq - 1)];
+        };
+        auto stage = [&](int32_t p, float2 uv, Stage& st) {
+            const Decode d = locate<CUBIC, STOCH>(a, (uint32_t)p * QPP + lane / TAPS, lane % TAPS, uv);
+            st.w = d.fin ? d.w : __builtin_nanf("");
+            st.sx = d.sx;
+            st.sy = d.sy;
+            float fx, fy;
+            const int i = latent_cell(d.sx, a.rx, a.LW, fx), j = latent_cell(d.sy, a.ry, a.LH, fy);
+            load_lat(st, i, j, fx, fy);
+        };
+        int32_t p = wave;
+        if (p >= npair) return;
+        stage(p, load_uv(p), S0);
+        float2 uv_next = load_uv(min(p + nwaves, npair));
+        auto turn = [&](const Stage& cur, Stage& nxt) {
+            const float2 uv_after = load_uv(min(p + 2 * nwaves, npair));
+            stage(p + nwaves, uv_next, nxt);
+            uv_next = uv_after;
+            one_pair(p, cur);
+            p += nwaves;
+            return p < npair;
+        };
+        while (turn(S0, S1) && turn(S1, S0)) {}
     }
 }
 
@@ -882,19 +1045,20 @@ void pack_weights(const float* mlp, Packed* pk)
         for (int mb = 0; mb < 2; ++mb) {
             if (h == 0)
                 for (int j = 0; j < 8; ++j) put(pk->a1[mb][lane], j, mlp[OFF_W1 + (32 * mb + m) * NL + j]);
-            else {
+            else
                 put_bias(pk->a1[mb][lane], mlp[OFF_B1 + 32 * mb + m]);
-                put_bias(pk->ab2[mb][lane], mlp[OFF_B2 + 32 * mb + m]);
-            }
             for (int kb = 0; kb < 4; ++kb)
                 for (int j = 0; j < 8; ++j)
                     put(pk->a2[mb][kb][lane], j, mlp[OFF_W2 + (32 * mb + m) * NH + hidden_of_slot(kb, h, j)]);
         }
-        for (int kb = 0; kb < 4; ++kb)
+        for (int kb2 = 0; kb2 < 2; ++kb2)
             for (int j = 0; j < 8; ++j)
-                put(pk->a3[kb][lane], j, m < NO ? mlp[OFF_W3 + m * NH + hidden_of_slot(kb, h, j)] : 0.0f);
-        if (h == 1 && m < NO) put_bias(pk->ab3[lane], mlp[OFF_B3 + m]);
+                put(pk->a3[kb2][lane], j, mlp[OFF_W3 + (lane % 8) * NH + hidden_of_slot3(kb2, lane / 16, j)]);
     }
+    for (int mb = 0; mb < 2; ++mb)
+        for (int h = 0; h < 2; ++h)
+            for (int r = 0; r < 16; ++r) pk->b2[h][mb][r] = mlp[OFF_B2 + row_of_acc(mb, h, r)];
+    for (int c = 0; c < NO; ++c) pk->b3[c / 4][c % 4] = mlp[OFF_B3 + c];
 }
 
 bool pow2_ratio(int big, int small)
