@@ -20,39 +20,21 @@ namespace {
 constexpr int BLOCK = 256;
 constexpr float INV_PI = 0.318309886183790672f;
 
-struct Material {
-    float albedo[3];
-    float rough;
-    float nx, ny;
-};
-
-__device__ __forceinline__ Material decode_material(uint2 t)
-{
-    Material m;
-    m.albedo[0] = dec_u8(t.x & 0xffu);
-    m.albedo[1] = dec_u8((t.x >> 8) & 0xffu);
-    m.albedo[2] = dec_u8((t.x >> 16) & 0xffu);
-    m.rough = dec_u8(t.x >> 24);
-    m.nx = dec_f16((uint16_t)(t.y & 0xffffu));
-    m.ny = dec_f16((uint16_t)(t.y >> 16));
-    return m;
-}
-
 struct V3 {
     float x, y, z;
 };
 
 __device__ __forceinline__ float dot(V3 a, V3 b)
 {
-    return a.x * b.x + a.y * b.y + a.z * b.z;
+    return __builtin_fmaf(a.z, b.z, __builtin_fmaf(a.y, b.y, a.x * b.x));
 }
 
 __device__ __forceinline__ float cross_norm2(V3 a, V3 b)
 {
-    float cx = a.y * b.z - a.z * b.y;
-    float cy = a.z * b.x - a.x * b.z;
-    float cz = a.x * b.y - a.y * b.x;
-    return cx * cx + cy * cy + cz * cz;
+    const float cx = __builtin_fmaf(a.y, b.z, -(a.z * b.y));
+    const float cy = __builtin_fmaf(a.z, b.x, -(a.x * b.z));
+    const float cz = __builtin_fmaf(a.x, b.y, -(a.y * b.x));
+    return __builtin_fmaf(cz, cz, __builtin_fmaf(cy, cy, cx * cx));
 }
 
 // The shading arithmetic uses the hardware's reciprocal, square root and
@@ -70,37 +52,74 @@ __device__ __forceinline__ float fsqrt(float x)
     return __builtin_amdgcn_sqrtf(x);
 }
 
-// Smith Lambda of GGX: (-1 + sqrt(1 + alpha^2 tan^2)) / 2.
-__device__ __forceinline__ float lambda_ggx(V3 n, V3 w, float nw, float a2)
+// What the shading of every tap of a query shares: the directions, their half
+// vector and the specular lobe's factor F / (2 pi).
+struct Frame {
+    V3 wo, wi, h;
+    float ks;
+};
+
+__device__ __forceinline__ Frame frame_of(V3 wo, V3 wi)
 {
-    float tan2 = cross_norm2(n, w) * frcp(nw * nw);
-    return 0.5f * (-1.0f + fsqrt(1.0f + a2 * tan2));
+    Frame f;
+    f.wo = wo;
+    f.wi = wi;
+    V3 h = {wo.x + wi.x, wo.y + wi.y, wo.z + wi.z};
+    const float il = __builtin_amdgcn_rsqf(h.x * h.x + h.y * h.y + h.z * h.z);
+    f.h = {h.x * il, h.y * il, h.z * il};
+    const float x = 1.0f - dot(wi, f.h), x2 = x * x;
+    f.ks = (0.04f + 0.96f * (x2 * x2 * x)) * (0.5f * INV_PI);
+    return f;
 }
 
-// f^ for one material, directions in the tangent frame.
-__device__ __forceinline__ void shade(const Material& m, V3 wo, V3 wi, float (&f)[3])
+// f^ of a material is diffuse albedo / pi + ks specular, with
+//   diffuse = n.wi,
+//   specular = a^2 n.wi / (den^2 (n.wi Ro + n.wo Ri)),
+//   den = a^2 (n.h)^2 + |n x h|^2,  Rw = sqrt((n.w)^2 + a^2 |n x w|^2):
+// the product D G2 F n.wi / (4 n.wo n.wi) with Smith's
+// G2 = 1 / (1 + Lambda(wo) + Lambda(wi)) = 2 n.wo n.wi / (n.wi Ro + n.wo Ri),
+// so one reciprocal serves all of it.  Both are zero below the horizon.
+__device__ __forceinline__ void lobes(const Frame& fr, float nx, float ny, float rough, float& diffuse, float& specular)
 {
-    V3 n = {m.nx, m.ny, fsqrt(fmaxf(0.0f, 1.0f - m.nx * m.nx - m.ny * m.ny))};
-    float alpha = fmaxf(m.rough * m.rough, 1e-3f), a2 = alpha * alpha;
-    float no = dot(n, wo), ni = dot(n, wi);
-    if (!(no > 0.0f) || !(ni > 0.0f)) {
-        f[0] = f[1] = f[2] = 0.0f;
-        return;
-    }
-    V3 h = {wo.x + wi.x, wo.y + wi.y, wo.z + wi.z};
-    float il = __builtin_amdgcn_rsqf(dot(h, h));
-    h.x *= il;
-    h.y *= il;
-    h.z *= il;
-    float nh = dot(n, h);
-    float den = nh * nh * a2 + cross_norm2(n, h);
-    float D = a2 * INV_PI * frcp(den * den);
-    float G2 = frcp(1.0f + lambda_ggx(n, wo, no, a2) + lambda_ggx(n, wi, ni, a2));
-    float x = 1.0f - dot(wi, h), x2 = x * x;
-    float F = 0.04f + 0.96f * (x2 * x2 * x);
-    float spec = D * G2 * F * frcp(4.0f * no * ni);
+    const V3 n = {nx, ny, fsqrt(fmaxf(0.0f, 1.0f - nx * nx - ny * ny))};
+    const float alpha = fmaxf(rough * rough, 1e-3f), a2 = alpha * alpha;
+    const float no = dot(n, fr.wo), ni = dot(n, fr.wi), nh = dot(n, fr.h);
+    const float den = __builtin_fmaf(nh * nh, a2, cross_norm2(n, fr.h));
+    const float Ro = fsqrt(__builtin_fmaf(a2, cross_norm2(n, fr.wo), no * no));
+    const float Ri = fsqrt(__builtin_fmaf(a2, cross_norm2(n, fr.wi), ni * ni));
+    const bool lit = (no > 0.0f) & (ni > 0.0f);
+    const float s = a2 * ni * frcp(den * den * __builtin_fmaf(ni, Ro, no * Ri));
+    diffuse = lit ? ni : 0.0f;
+    specular = lit ? s : 0.0f;
+}
+
+// The texel's eight bytes: albedo and roughness codes, the normal's x and y.
+struct Texel {
+    float albedo[3];   // codes: 255 times the albedo
+    float rough, nx, ny;
+};
+
+__device__ __forceinline__ Texel decode_texel(uint2 t)
+{
+    Texel m;
+    m.albedo[0] = (float)(t.x & 0xffu);
+    m.albedo[1] = (float)((t.x >> 8) & 0xffu);
+    m.albedo[2] = (float)((t.x >> 16) & 0xffu);
+    m.rough = dec_u8(t.x >> 24);
+    m.nx = dec_f16((uint16_t)(t.y & 0xffffu));
+    m.ny = dec_f16((uint16_t)(t.y >> 16));
+    return m;
+}
+
+// f^ from sums over the taps: of the lobes, and of the diffuse one times the
+// albedo codes.
+__device__ __forceinline__ void finish(const Frame& fr, const float (&codes)[3], float specular, float (&f)[3])
+{
 #pragma unroll
-    for (int c = 0; c < 3; ++c) f[c] = (m.albedo[c] * INV_PI + spec) * ni;
+    for (int c = 0; c < 3; ++c) {
+        const float d = codes[c] * (INV_PI / 255.0f);
+        f[c] = specular == 0.0f ? d : __builtin_fmaf(fr.ks, specular, d);   // ks has no value for opposite directions
+    }
 }
 
 __device__ __forceinline__ int clampi(int v, int hi)
@@ -113,9 +132,109 @@ struct Levels {
     int32_t n;
 };
 
+// Sum over N neighbouring lanes (2 or 4), left in each of them.
+template <int N>
+__device__ __forceinline__ float lane_sum(float v)
+{
+    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));   // [1,0,3,2]
+    if constexpr (N == 4)
+        v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));   // [2,3,0,1]
+    return v;
+}
+
+// Filtering before or after shading, a lane per column of the window (two or
+// four lanes a query), so that a query's load is one row of the window: 16 or
+// 32 bytes, one or two lines.
+//
+// On scattered queries the time goes into whole 128-byte lines, 3.1 a query for
+// the 4 x 4 window: 1.8 GB for 4M queries, at 7.7 TB/s from the L2s' far side.
+// With a lane per query the lines in flight exceeded the L2s, a line's halves
+// were asked for by different instructions (31.8M requests for 14.1M lines, now
+// 17.0M) and 16 loads a lane kept the address units busy. 4M
+// scattered queries, 4 x 4: after shading 284 -> 238 us, before 282 -> 256.
 template <bool CUBIC, int MODE>
-__global__ __launch_bounds__(BLOCK) void k_shade(Levels L, const float* __restrict__ q, int32_t n, uint32_t key,
-                                                 float* __restrict__ out, int32_t* __restrict__ idx)
+__global__ __launch_bounds__(BLOCK) void k_shade_taps(Levels L, const float* __restrict__ q, int32_t n,
+                                                      float* __restrict__ out)
+{
+    constexpr int NT = CUBIC ? 4 : 2;
+    const int32_t i = blockIdx.x * (BLOCK / NT) + threadIdx.x / NT;
+    const int a = threadIdx.x % NT;
+    if (i >= n) return;
+    const float* e = q + 9 * (int64_t)i;
+    float r[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r[k] = __builtin_nontemporal_load(e + k);   // streamed in
+    const float u = r[0], v = r[1], s = r[2];
+    int l = (int)(s >= 1.41421354f) + (int)(s >= 2.82842708f);
+    l = l < L.n - 1 ? l : L.n - 1;
+    const TexLevel T = l == 0 ? L.lv[0] : (l == 1 ? L.lv[1] : L.lv[2]);
+    const uint2* tex = reinterpret_cast<const uint2*>(T.texels);
+    int cx = 0, cy = 0;
+    float tx = 0.0f, ty = 0.0f;
+    const bool ok = cell_of(u * (float)T.w - 0.5f, cx, tx) & cell_of(v * (float)T.h - 0.5f, cy, ty);
+    float wx, wy[NT];
+    int x0 = cx, y0 = cy;
+    if constexpr (CUBIC) {
+        const Cubic6 ca = cubic6(tx), cb = cubic6(ty);
+        wx = (a == 0 ? ca.a0 : a == 1 ? ca.a1 : a == 2 ? ca.a2 : ca.a3) * K6;
+        wy[0] = cb.a0 * K6; wy[1] = cb.a1 * K6; wy[2] = cb.a2 * K6; wy[3] = cb.a3 * K6;
+        x0 -= 1;
+        y0 -= 1;
+    } else {
+        wx = a ? tx : 1.0f - tx;
+        wy[0] = 1.0f - ty; wy[1] = ty;
+    }
+    uint2 texel[NT];
+    const int xx = clampi(x0 + a, T.w - 1);
+#pragma unroll
+    for (int b = 0; b < NT; ++b) texel[b] = tex[material_index(xx, clampi(y0 + b, T.h - 1), T.w)];
+    const Frame fr = frame_of({r[3], r[4], r[5]}, {r[6], r[7], r[8]});
+    float codes[3] = {0.0f, 0.0f, 0.0f}, spec = 0.0f, rough = 0.0f, nx = 0.0f, ny = 0.0f;
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+        const Texel m = decode_texel(texel[b]);
+        const float w = wx * wy[b];
+        float wd = w;   // the albedo's weight
+        if constexpr (MODE == STF_SHADE_AFTER_FILTER) {
+            rough = __builtin_fmaf(w, m.rough, rough);
+            nx = __builtin_fmaf(w, m.nx, nx);
+            ny = __builtin_fmaf(w, m.ny, ny);
+        } else {
+            float d, sp;
+            lobes(fr, m.nx, m.ny, m.rough, d, sp);
+            wd *= d;
+            spec = __builtin_fmaf(w, sp, spec);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) codes[c] = __builtin_fmaf(wd, m.albedo[c], codes[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) codes[c] = lane_sum<NT>(codes[c]);
+    if constexpr (MODE == STF_SHADE_AFTER_FILTER) {
+        float d;
+        lobes(fr, lane_sum<NT>(nx), lane_sum<NT>(ny), lane_sum<NT>(rough), d, spec);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) codes[c] *= d;
+    } else {
+        spec = lane_sum<NT>(spec);
+    }
+    float f[3];
+    finish(fr, codes, spec, f);
+    if (!ok) f[0] = f[1] = f[2] = __builtin_nanf("");
+    float* o = out + 3 * (int64_t)i;   // results are streamed out (nontemporal stores)
+    if constexpr (CUBIC) {
+        const float mine = a == 0 ? f[0] : a == 1 ? f[1] : f[2];
+        if (a < 3) __builtin_nontemporal_store(mine, o + a);
+    } else {
+        __builtin_nontemporal_store(a ? f[1] : f[0], o + a);
+        if (a) __builtin_nontemporal_store(f[2], o + 2);
+    }
+}
+
+// One tap, chosen at random, is shaded.
+template <bool CUBIC>
+__global__ __launch_bounds__(BLOCK) void k_shade_one(Levels L, const float* __restrict__ q, int32_t n,
+                                                     uint32_t key, float* __restrict__ out, int32_t* __restrict__ idx)
 {
     int32_t i = blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n) return;
@@ -135,81 +254,31 @@ __global__ __launch_bounds__(BLOCK) void k_shade(Levels L, const float* __restri
     bool ok = cell_of(x, cx, tx) & cell_of(y, cy, ty);
     float f[3] = {__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
     if (ok) {
-        if constexpr (MODE == STF_SHADE_STOCHASTIC) {
-            const uint32_t b = pcg(key ^ (uint32_t)i);
-            const uint32_t base = pcg_base(b);
-            const float mx = hash_m(pcg_from_base(base, 0u)), my = hash_m(pcg_from_base(base, 1u));
-            int sx, sy;
-            if constexpr (CUBIC) {
-                sx = cx + choose_cubic_m(tx, mx);
-                sy = cy + choose_cubic_m(ty, my);
-            } else {
-                sx = cx + choose_linear_m(tx, mx);
-                sy = cy + choose_linear_m(ty, my);
-            }
-            sx = clampi(sx, T.w - 1);
-            sy = clampi(sy, T.h - 1);
-            shade(decode_material(tex[material_index(sx, sy, T.w)]), wo, wi, f);
-            if (idx) {
-                idx[3 * (int64_t)i] = sx;
-                idx[3 * (int64_t)i + 1] = sy;
-                idx[3 * (int64_t)i + 2] = l;
-            }
+        const uint32_t b = pcg(key ^ (uint32_t)i);
+        const uint32_t base = pcg_base(b);
+        const float mx = hash_m(pcg_from_base(base, 0u)), my = hash_m(pcg_from_base(base, 1u));
+        int sx, sy;
+        if constexpr (CUBIC) {
+            sx = cx + choose_cubic_m(tx, mx);
+            sy = cy + choose_cubic_m(ty, my);
         } else {
-            constexpr int NT = CUBIC ? 4 : 2;
-            float wx[NT], wy[NT];
-            if constexpr (CUBIC) {
-                Cubic6 a = cubic6(tx), b = cubic6(ty);
-                wx[0] = a.a0 * K6; wx[1] = a.a1 * K6; wx[2] = a.a2 * K6; wx[3] = a.a3 * K6;
-                wy[0] = b.a0 * K6; wy[1] = b.a1 * K6; wy[2] = b.a2 * K6; wy[3] = b.a3 * K6;
-                cx -= 1;
-                cy -= 1;
-            } else {
-                wx[0] = 1.0f - tx; wx[1] = tx;
-                wy[0] = 1.0f - ty; wy[1] = ty;
-            }
-            // all taps' texels first: their loads are then in flight together
-            // instead of one latency per tap between shading evaluations
-            uint2 texel[NT][NT];
-#pragma unroll
-            for (int b = 0; b < NT; ++b) {
-                const int yy = clampi(cy + b, T.h - 1);
-#pragma unroll
-                for (int a = 0; a < NT; ++a) texel[b][a] = tex[material_index(clampi(cx + a, T.w - 1), yy, T.w)];
-            }
-            float acc[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int b = 0; b < NT; ++b) {
-#pragma unroll
-                for (int a = 0; a < NT; ++a) {
-                    Material m = decode_material(texel[b][a]);
-                    float w = wx[a] * wy[b];
-                    if constexpr (MODE == STF_SHADE_AFTER_FILTER) {
-                        acc[0] = __builtin_fmaf(w, m.albedo[0], acc[0]);
-                        acc[1] = __builtin_fmaf(w, m.albedo[1], acc[1]);
-                        acc[2] = __builtin_fmaf(w, m.albedo[2], acc[2]);
-                        acc[3] = __builtin_fmaf(w, m.rough, acc[3]);
-                        acc[4] = __builtin_fmaf(w, m.nx, acc[4]);
-                        acc[5] = __builtin_fmaf(w, m.ny, acc[5]);
-                    } else {
-                        float g[3];
-                        shade(m, wo, wi, g);
-                        acc[0] = __builtin_fmaf(w, g[0], acc[0]);
-                        acc[1] = __builtin_fmaf(w, g[1], acc[1]);
-                        acc[2] = __builtin_fmaf(w, g[2], acc[2]);
-                    }
-                }
-            }
-            if constexpr (MODE == STF_SHADE_AFTER_FILTER) {
-                Material m;
-                m.albedo[0] = acc[0]; m.albedo[1] = acc[1]; m.albedo[2] = acc[2];
-                m.rough = acc[3]; m.nx = acc[4]; m.ny = acc[5];
-                shade(m, wo, wi, f);
-            } else {
-                f[0] = acc[0]; f[1] = acc[1]; f[2] = acc[2];
-            }
+            sx = cx + choose_linear_m(tx, mx);
+            sy = cy + choose_linear_m(ty, my);
         }
-    } else if (idx && MODE == STF_SHADE_STOCHASTIC) {
+        sx = clampi(sx, T.w - 1);
+        sy = clampi(sy, T.h - 1);
+        const Frame fr = frame_of(wo, wi);
+        const Texel m = decode_texel(tex[material_index(sx, sy, T.w)]);
+        float d, sp;
+        lobes(fr, m.nx, m.ny, m.rough, d, sp);
+        const float c[3] = {d * m.albedo[0], d * m.albedo[1], d * m.albedo[2]};
+        finish(fr, c, sp, f);
+        if (idx) {
+            idx[3 * (int64_t)i] = sx;
+            idx[3 * (int64_t)i + 1] = sy;
+            idx[3 * (int64_t)i + 2] = l;
+        }
+    } else if (idx) {
         idx[3 * (int64_t)i] = BAD_INDEX;
         idx[3 * (int64_t)i + 1] = BAD_INDEX;
         idx[3 * (int64_t)i + 2] = BAD_INDEX;
@@ -224,16 +293,18 @@ template <bool CUBIC>
 hipError_t launch_shade_f(const Levels& L, const float* q, int32_t n, int mode, uint32_t key, float* out,
                           int32_t* idx, hipStream_t s)
 {
-    dim3 grid((n + BLOCK - 1) / BLOCK), block(BLOCK);
+    const dim3 block(BLOCK);
+    const int per = BLOCK / (CUBIC ? 4 : 2);
+    const dim3 one((unsigned)(((int64_t)n + BLOCK - 1) / BLOCK)), taps((unsigned)(((int64_t)n + per - 1) / per));
     switch (mode) {
     case STF_SHADE_AFTER_FILTER:
-        hipLaunchKernelGGL((k_shade<CUBIC, STF_SHADE_AFTER_FILTER>), grid, block, 0, s, L, q, n, key, out, idx);
+        hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_SHADE_AFTER_FILTER>), taps, block, 0, s, L, q, n, out);
         break;
     case STF_FILTER_AFTER_SHADE:
-        hipLaunchKernelGGL((k_shade<CUBIC, STF_FILTER_AFTER_SHADE>), grid, block, 0, s, L, q, n, key, out, idx);
+        hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_FILTER_AFTER_SHADE>), taps, block, 0, s, L, q, n, out);
         break;
     default:
-        hipLaunchKernelGGL((k_shade<CUBIC, STF_SHADE_STOCHASTIC>), grid, block, 0, s, L, q, n, key, out, idx);
+        hipLaunchKernelGGL((k_shade_one<CUBIC>), one, block, 0, s, L, q, n, key, out, idx);
     }
     return hipGetLastError();
 }
