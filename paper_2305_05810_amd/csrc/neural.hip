@@ -219,19 +219,29 @@ __device__ __forceinline__ f32x4 mask4(f32x4 v, const f32x4& h)   // v where h >
 // from the same LDS matrices with the sample in the k-slot, 4 bytes a lane,
 // and each tile's sum, formed from zero, is added to the wave's registers.
 //
-// 608 matrix instructions of 32 cycles per tile would take 65 us for 262,144
+// 600 matrix instructions of 32 cycles per tile would take 64 us for 262,144
 // samples on 1,024 SIMDs; the chain of seven barriers per tile, each with an
-// LDS round trip and a dependent chain, holds the pass at 129 us (matrix cores
-// busy 50% of the cycles; without the atomics 127 us, without the gathers 122
-// us).  Four waves per SIMD from two blocks per CU fill each other's gaps, and
-// a tile's gathers are issued a tile ahead.  The same products as register-
-// blocked FMAs from LDS took 220 us.
+// LDS round trip and a dependent chain, holds the pass at 107 us.  Four waves
+// per SIMD from two blocks per CU fill each other's gaps, and a tile's gathers
+// are issued a tile ahead.  The products that not all waves share (the output,
+// the latents' gradient, dW3) go to one wave per SIMD: with both halves of a
+// product on one SIMD the pass took 124 us.  Left alone, the later block of a
+// CU falls behind by a third per tile and ends alone; with the raised priority
+// it falls behind by a fifth, as two blocks of evenly placed products do, so
+// that the latents' atomics meet in nearly the same order from one arrangement
+// to another (2.4% of the sums differ in their rounding, as between two runs;
+// 3.6% without).  The same products as register-blocked FMAs from LDS took 220
+// us.
 __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
 {
     __shared__ __align__(16) char smem[sizeof(TrainShared)];
     TrainShared& S = *reinterpret_cast<TrainShared*>(smem);
     const int t = threadIdx.x, lane = t % 64, wave = t / 64, n = lane % 16, g = lane / 16;
     const int mb = wave % 4, nh = wave / 4;
+    // Two waves share a SIMD (waves 4 apart).  What only some waves do is given
+    // to one wave per SIMD: the output of either sample half (SIMDs 0, 1), the
+    // latents' gradient of either half (2, 3), a unit block of dW3 (all four).
+    const bool makes_y = mb == nh, makes_dz = mb == 2 + nh, makes_w3 = !makes_y && !makes_dz;
     {   // Operand images: every weight is loaded once and put where its images
         // hold it -- lane l of an A operand holds row l % 16, k-slot l / 16.
         float* w2 = reinterpret_cast<float*>(S.w2);
@@ -279,9 +289,9 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
     const int smp = 16 * nh + n, row0 = train_row(smp) + 4 * g, col0 = train_row(g) + n;
     // gradients over the block's tiles: dW2 rows of block mb, columns of
     // blocks 2 nh and 2 nh + 1; dW1 and db1 (nh = 0: column 8) or db2 (nh = 1:
-    // column 8); dW3 of unit block 2 (mb - 2) + nh (mb >= 2); db3
-    f32x4 g20 = (f32x4)0.0f, g21 = g20, g1 = g20, g3 = g20, gb3 = g20;
-    float lacc = 0.0f;
+    // column 8); dW3 of unit block mb (makes_w3); db3 (wave 0)
+    f32x4 g20 = (f32x4)0.0f, g21 = g20, g1 = g20, g3 = g20;
+    float gb3 = 0.0f, lacc = 0.0f;
     const int s8 = t % 256 / 8, k8 = t % 8, c8 = 2 * (k8 % 4) + k8 / 4;
     const bool latents = t < 256;
     const int32_t ntiles = (a.B - 1) / TS + 1;
@@ -298,6 +308,10 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
         } else {
             S.t[s8 * NO + c8] = cur.v0;
         }
+        // the later one of a CU's two blocks, whose waves are served after the
+        // earlier one's, goes first in every fourth tile (see above)
+        __builtin_amdgcn_s_setprio(0);
+        if (blockIdx.x >= TRAIN_BLOCKS / 2 && tile / TRAIN_BLOCKS % 4 == 0) __builtin_amdgcn_s_setprio(1);
         __syncthreads();   // z, t; the previous tile is done with the matrices
         if (latents) train_scatter(a, prev, S.y[s8 * ZSTRIDE + c8]);
         prev = cur;
@@ -317,7 +331,7 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
         h2 = relu4(train_chain(&S.w2[4 * mb], S.h1 + row0, lane, h2));
         *reinterpret_cast<f32x4*>(&S.h2d1[own]) = h2;
         __syncthreads();
-        if (mb == 0) {   // Y = W3 H2 + b3, the loss and its gradient
+        if (makes_y) {   // Y = W3 H2 + b3, the loss and its gradient
             const f32x4 y = train_chain(S.w3, S.h2d1 + row0, lane, *reinterpret_cast<const f32x4*>(&S.b3[4 * g]));
             const float2 target = *reinterpret_cast<const float2*>(&S.t[smp * NO + 2 * g]);
             const float e0 = y[0] - target.x, e1 = y[1] - target.y;
@@ -332,16 +346,17 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
             d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t[1], dy.y, d2, 0, 0, 0);
             *reinterpret_cast<f32x4*>(&S.d2[own]) = mask4(d2, h2);
         }
-        if (mb >= 2) {   // dW3^T += H2 dY^T; db3 += 1 dY^T
-            const float* u = S.h2d1 + col0 + 16 * (2 * (mb - 2) + nh);
-            f32x4 s0 = (f32x4)0.0f, s1 = (f32x4)0.0f;
+        if (makes_w3) {   // dW3^T += H2 dY^T
+            const float* u = S.h2d1 + col0 + 16 * mb;
+            f32x4 s0 = (f32x4)0.0f;
 #pragma unroll
-            for (int j = 0; j < TS / 4; ++j) {
-                const float dy = S.y[(4 * j + g) * ZSTRIDE + n];
-                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(u[train_row(4 * j)], dy, s0, 0, 0, 0);
-                if (wave == 2) s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, dy, s1, 0, 0, 0);
-            }
+            for (int j = 0; j < TS / 4; ++j)
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(u[train_row(4 * j)], S.y[(4 * j + g) * ZSTRIDE + n], s0, 0, 0, 0);
             g3 += s0;
+        } else if (wave == 0) {   // db3 += dY 1, a lane per column
+            float s1 = 0.0f;
+#pragma unroll
+            for (int k = 0; k < TS; ++k) s1 += S.y[k * ZSTRIDE + n];
             gb3 += s1;
         }
         __syncthreads();
@@ -361,7 +376,7 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
             g21 += s1;
         }
         __syncthreads();
-        if (mb == 1) {   // dZ = W1^T D1, scattered by the next tile's gather threads
+        if (makes_dz) {   // dZ = W1^T D1, scattered by the next tile's gather threads
             const f32x4 dz = train_chain(S.w1t, S.h2d1 + row0, lane, (f32x4)0.0f);
             *reinterpret_cast<float2*>(&S.y[smp * ZSTRIDE + 2 * g]) = make_float2(dz[0], dz[1]);
         }
@@ -388,10 +403,10 @@ __global__ __launch_bounds__(TBLOCK, 4) void k_ntex_train(TrainArgs a)
         out[OFF_W2 + u * NH + 32 * nh + 16 + col] = g21[r];
         if (nh == 0 && n < NL) out[OFF_W1 + u * NL + ch] = g1[r];
         if (n == 8) out[(nh ? OFF_B2 : OFF_B1) + u] = g1[r];
-        if (mb >= 2 && n < NL) out[OFF_W3 + ch * NH + 16 * (2 * (mb - 2) + nh) + 4 * r + g] = g3[r];
+        if (makes_w3 && n < NL) out[OFF_W3 + ch * NH + u] = g3[r];
     }
-    if (wave == 2 && lane < NO) out[OFF_B3 + ch] = gb3[0];
-    if (mb == 0) {
+    if (wave == 0 && lane < NO) out[OFF_B3 + ch] = gb3;
+    if (makes_y) {
         for (int off = 32; off > 0; off >>= 1) lacc += __shfl_xor(lacc, off);
         if (lane == 0) S.t[nh] = lacc;
     }
