@@ -151,7 +151,7 @@ __device__ __forceinline__ float lane_sum(float v)
 // With a lane per query the lines in flight exceeded the L2s, a line's halves
 // were asked for by different instructions (31.8M requests for 14.1M lines, now
 // 17.0M) and 16 loads a lane kept the address units busy. 4M
-// scattered queries, 4 x 4: after shading 284 -> 238 us, before 282 -> 256.
+// scattered queries, 4 x 4: after shading 284 -> 238 us, before 282 -> 238.
 template <bool CUBIC, int MODE>
 __global__ __launch_bounds__(BLOCK) void k_shade_taps(Levels L, const float* __restrict__ q, int32_t n,
                                                       float* __restrict__ out)
@@ -164,6 +164,8 @@ __global__ __launch_bounds__(BLOCK) void k_shade_taps(Levels L, const float* __r
     float r[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) r[k] = __builtin_nontemporal_load(e + k);   // streamed in
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(r[k]));   // all of the record at once (see k_shade_one)
     const float u = r[0], v = r[1], s = r[2];
     int l = (int)(s >= 1.41421354f) + (int)(s >= 2.82842708f);
     l = l < L.n - 1 ? l : L.n - 1;
@@ -242,6 +244,10 @@ __global__ __launch_bounds__(BLOCK) void k_shade_one(Levels L, const float* __re
     float r[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) r[k] = __builtin_nontemporal_load(e + k);   // streamed in
+    // all of the record at once: loads moved behind the wait for the position
+    // find its lines evicted (112 us for 4M scattered queries, 97 so)
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(r[k]));
     float u = r[0], v = r[1], s = r[2];
     V3 wo = {r[3], r[4], r[5]}, wi = {r[6], r[7], r[8]};
     int l = (int)(s >= 1.41421354f) + (int)(s >= 2.82842708f);
