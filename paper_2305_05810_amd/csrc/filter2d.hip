@@ -435,6 +435,47 @@ __device__ __forceinline__ void gauss_discrete_weights(double t, double inv2s2, 
 // The discrete Gaussian mean (normalised 4x4 window) as a deterministic kind.
 constexpr int KIND_GAUSS_MEAN = 100;
 
+template <int CAP>
+__device__ __forceinline__ void dct_load_words(const DctSrc<CAP>& S, int bx, int by, uint4 (&w4)[CAP / 4])
+{
+    const uint4* b = reinterpret_cast<const uint4*>(S.blocks + ((int64_t)by * S.BW + bx) * CAP);
+#pragma unroll
+    for (int g = 0; g < CAP / 4; ++g) w4[g] = b[g];
+}
+
+// Adds a block's channels (`left` of the four words) to their sums, a whole
+// group without a test between them.  By value: the two ways' common code,
+// merged over references, would index the sums at run time.
+__device__ __forceinline__ float4 dct_add_group(uint4 w, DctFactors F, int left, float4 a)
+{
+    if (left >= 4) {
+        a.x = dct_accumulate(dct_codes(w.x), F, a.x);
+        a.y = dct_accumulate(dct_codes(w.y), F, a.y);
+        a.z = dct_accumulate(dct_codes(w.z), F, a.z);
+        a.w = dct_accumulate(dct_codes(w.w), F, a.w);
+    } else {
+        if (left > 0) a.x = dct_accumulate(dct_codes(w.x), F, a.x);
+        if (left > 1) a.y = dct_accumulate(dct_codes(w.y), F, a.y);
+        if (left > 2) a.z = dct_accumulate(dct_codes(w.z), F, a.z);
+    }
+    return a;
+}
+
+template <int CAP>
+__device__ __forceinline__ void dct_add_words(const uint4 (&w4)[CAP / 4], const DctFactors& F, int C,
+                                              float (&acc)[CAP])
+{
+#pragma unroll
+    for (int g = 0; g < CAP / 4; ++g) {
+        const float4 a = dct_add_group(w4[g], F, C - 4 * g,
+                                       make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]));
+        acc[4 * g] = a.x;
+        acc[4 * g + 1] = a.y;
+        acc[4 * g + 2] = a.z;
+        acc[4 * g + 3] = a.w;
+    }
+}
+
 // Deterministic filtering of a DCT texture by blocks (dct_decode.h): the
 // window's weight sums per axis and block, then six multiply-adds per channel
 // and block the window meets, instead of decoding each of its 4 or 16 texels.
@@ -452,7 +493,7 @@ constexpr int KIND_GAUSS_MEAN = 100;
 // would take 75 us of the frame below).  4K frame of a 4096^2 set of 9
 // channels, 16 taps: 507 us with each texel of the taps' box decoded into
 // LDS once, 124 us so; 2M uniform uv: 228 us decoding every tap, 106 us so;
-// 4 taps, 4 channels, 2M pixels of a frame: 20.9 and 17.0 us.  An unguarded
+// 4 taps, 4 channels, 2M pixels of a frame: 20.9 and 15.2 us.  An unguarded
 // group of four channels lets its LDS reads overlap (a test per channel: 141
 // us); tiles of 16, 20 and 32 KiB: 127, 124 and 147 us (the last one leaves 4
 // blocks per CU).
@@ -466,7 +507,7 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
                                                    int scatter, unsigned long long* __restrict__ counters, float sigma)
 {
     constexpr int NT = KIND == KIND_LINEAR ? 2 : 4;
-        constexpr int TILE = STAGE ? STAGE_FLOATS : BLOCK * CAP;
+    constexpr int TILE = STAGE ? STAGE_FLOATS : BLOCK * CAP;
     static_assert(BLOCK * CAP <= TILE, "the tile also stages the block's results");
     __shared__ __align__(16) float tile[TILE];
     __shared__ float2 cosines[8];
@@ -578,57 +619,71 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
 #pragma unroll
     for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
     const bool use = live && ok;
-    // the (at most) four blocks; a second block without taps has weight 0
-    const int nv = __any(use && py.blk1 != py.blk0) ? 2 : 1, nu = __any(use && px.blk1 != px.blk0) ? 2 : 1;
+    if constexpr (!STAGE) {
+        // The first block, then the lane's second one along x or y (along
+        // neither: weight 0), their words in flight together, then for lanes
+        // with taps in four blocks the other two.  On scattered queries a wave
+        // meets all four, but a lane in 64 has four: block after block for the
+        // whole wave 6M random uv of 9 channels take 297 us, so 146 (4
+        // channels, 2M: 69 and 26).
+        const bool sx = px.blk1 != px.blk0, sy = py.blk1 != py.blk0;
+        const bool more = __any(use && (sx || sy));
+        uint4 w0[CAP / 4], w1[CAP / 4];
+        dct_load_words(S, px.blk0, py.blk0, w0);
+        if (more) dct_load_words(S, px.blk1, sx ? py.blk0 : py.blk1, w1);
+        const DctRow r0 = dct_row({py.a0.s0 * inv, py.a0.s1 * inv, py.a0.s2 * inv});
+        const DctRow r1 = dct_row({py.a1.s0 * inv, py.a1.s1 * inv, py.a1.s2 * inv});
+        dct_add_words<CAP>(w0, dct_factors(r0, px.a0), C, acc);
+        if (more) {
+            const DctRow r = {sx ? r0.dc : r1.dc, sx ? r0.k0 : r1.k0, sx ? r0.k1 : r1.k1, sx ? r0.k2 : r1.k2,
+                              sx ? r0.k11 : r1.k11};
+            const DctAxis a = {sx ? px.a1.s0 : px.a0.s0, sx ? px.a1.s1 : px.a0.s1, sx ? px.a1.s2 : px.a0.s2};
+            dct_add_words<CAP>(w1, dct_factors(r, a), C, acc);
+            if (use && sx && sy) {
+                dct_load_words(S, px.blk0, py.blk1, w0);
+                dct_load_words(S, px.blk1, py.blk1, w1);
+                dct_add_words<CAP>(w0, dct_factors(r1, px.a0), C, acc);
+                dct_add_words<CAP>(w1, dct_factors(r1, px.a1), C, acc);
+            }
+        }
+    } else {
+        // the (at most) four blocks; a second block without taps has weight 0
+        const int nv = __any(use && py.blk1 != py.blk0) ? 2 : 1, nu = __any(use && px.blk1 != px.blk0) ? 2 : 1;
 #pragma unroll 1
-    for (int v = 0; v < nv; ++v) {
-        const DctRow row = dct_row({(v ? py.a1.s0 : py.a0.s0) * inv, (v ? py.a1.s1 : py.a0.s1) * inv,
-                                    (v ? py.a1.s2 : py.a0.s2) * inv});
-        const int by = v ? py.blk1 : py.blk0;
+        for (int v = 0; v < nv; ++v) {
+            const DctRow row = dct_row({(v ? py.a1.s0 : py.a0.s0) * inv, (v ? py.a1.s1 : py.a0.s1) * inv,
+                                        (v ? py.a1.s2 : py.a0.s2) * inv});
+            const int by = v ? py.blk1 : py.blk0;
 #pragma unroll 1
-        for (int u = 0; u < nu; ++u) {
-            const DctFactors F = dct_factors(row, {u ? px.a1.s0 : px.a0.s0, u ? px.a1.s1 : px.a0.s1,
-                                                   u ? px.a1.s2 : px.a0.s2});
-            const int bx = u ? px.blk1 : px.blk0;
-            // whole groups of four channels without a test between them
-            if (stage) {   // (a query without a cell reads the first block)
-                const float* e = tile + (use ? ((by - by0) * nbx + (bx - bx0)) * bstride : 0);
-                auto one = [&](int c) {
-                    const float4 k0 = *reinterpret_cast<const float4*>(e + 8 * c);
-                    const float2 k1 = *reinterpret_cast<const float2*>(e + 8 * c + 4);
-                    acc[c] = dct_accumulate({k0.x, k0.y, k0.z, k0.w, k1.x, k1.y}, F, acc[c]);
-                };
+            for (int u = 0; u < nu; ++u) {
+                const DctFactors F = dct_factors(row, {u ? px.a1.s0 : px.a0.s0, u ? px.a1.s1 : px.a0.s1,
+                                                       u ? px.a1.s2 : px.a0.s2});
+                const int bx = u ? px.blk1 : px.blk0;
+                // whole groups of four channels without a test between them
+                if (stage) {   // (a query without a cell reads the first block)
+                    const float* e = tile + (use ? ((by - by0) * nbx + (bx - bx0)) * bstride : 0);
+                    auto one = [&](int c) {
+                        const float4 k0 = *reinterpret_cast<const float4*>(e + 8 * c);
+                        const float2 k1 = *reinterpret_cast<const float2*>(e + 8 * c + 4);
+                        acc[c] = dct_accumulate({k0.x, k0.y, k0.z, k0.w, k1.x, k1.y}, F, acc[c]);
+                    };
 #pragma unroll
-                for (int g = 0; g < CAP; g += 4) {
-                    if (g + 4 <= C) {
-                        one(g);
-                        one(g + 1);
-                        one(g + 2);
-                        one(g + 3);
-                    } else {
-                        if (g < C) one(g);
-                        if (g + 1 < C) one(g + 1);
-                        if (g + 2 < C) one(g + 2);
+                    for (int g = 0; g < CAP; g += 4) {
+                        if (g + 4 <= C) {
+                            one(g);
+                            one(g + 1);
+                            one(g + 2);
+                            one(g + 3);
+                        } else {
+                            if (g < C) one(g);
+                            if (g + 1 < C) one(g + 1);
+                            if (g + 2 < C) one(g + 2);
+                        }
                     }
-                }
-            } else {
-                const uint4* b = reinterpret_cast<const uint4*>(S.blocks + ((int64_t)by * S.BW + bx) * CAP);
-                uint4 w4[CAP / 4];
-#pragma unroll
-                for (int g = 0; g < CAP / 4; ++g) w4[g] = b[g];
-                auto one = [&](int c, uint32_t w) { acc[c] = dct_accumulate(dct_codes(w), F, acc[c]); };
-#pragma unroll
-                for (int g = 0; g < CAP / 4; ++g) {
-                    if (4 * g + 4 <= C) {
-                        one(4 * g, w4[g].x);
-                        one(4 * g + 1, w4[g].y);
-                        one(4 * g + 2, w4[g].z);
-                        one(4 * g + 3, w4[g].w);
-                    } else {
-                        if (4 * g < C) one(4 * g, w4[g].x);
-                        if (4 * g + 1 < C) one(4 * g + 1, w4[g].y);
-                        if (4 * g + 2 < C) one(4 * g + 2, w4[g].z);
-                    }
+                } else {
+                    uint4 w4[CAP / 4];
+                    dct_load_words(S, bx, by, w4);
+                    dct_add_words<CAP>(w4, F, C, acc);
                 }
             }
         }
