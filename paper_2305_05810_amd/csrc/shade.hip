@@ -24,12 +24,23 @@ struct V3 {
     float x, y, z;
 };
 
+// Each operation rounded by itself: what decides the horizon and the specular
+// peak, whose width is down to alpha = 1e-3, keeps its rounding.
 __device__ __forceinline__ float dot(V3 a, V3 b)
 {
-    return __builtin_fmaf(a.z, b.z, __builtin_fmaf(a.y, b.y, a.x * b.x));
+    return a.x * b.x + a.y * b.y + a.z * b.z;
 }
 
 __device__ __forceinline__ float cross_norm2(V3 a, V3 b)
+{
+    const float cx = a.y * b.z - a.z * b.y;
+    const float cy = a.z * b.x - a.x * b.z;
+    const float cz = a.x * b.y - a.y * b.x;
+    return cx * cx + cy * cy + cz * cz;
+}
+
+// Fused, for the shadowing terms, which are smooth.
+__device__ __forceinline__ float cross_norm2_fma(V3 a, V3 b)
 {
     const float cx = __builtin_fmaf(a.y, b.z, -(a.z * b.y));
     const float cy = __builtin_fmaf(a.z, b.x, -(a.x * b.z));
@@ -84,9 +95,9 @@ __device__ __forceinline__ void lobes(const Frame& fr, float nx, float ny, float
     const V3 n = {nx, ny, fsqrt(fmaxf(0.0f, 1.0f - nx * nx - ny * ny))};
     const float alpha = fmaxf(rough * rough, 1e-3f), a2 = alpha * alpha;
     const float no = dot(n, fr.wo), ni = dot(n, fr.wi), nh = dot(n, fr.h);
-    const float den = __builtin_fmaf(nh * nh, a2, cross_norm2(n, fr.h));
-    const float Ro = fsqrt(__builtin_fmaf(a2, cross_norm2(n, fr.wo), no * no));
-    const float Ri = fsqrt(__builtin_fmaf(a2, cross_norm2(n, fr.wi), ni * ni));
+    const float den = nh * nh * a2 + cross_norm2(n, fr.h);
+    const float Ro = fsqrt(__builtin_fmaf(a2, cross_norm2_fma(n, fr.wo), no * no));
+    const float Ri = fsqrt(__builtin_fmaf(a2, cross_norm2_fma(n, fr.wi), ni * ni));
     const bool lit = (no > 0.0f) & (ni > 0.0f);
     const float s = a2 * ni * frcp(den * den * __builtin_fmaf(ni, Ro, no * Ri));
     diffuse = lit ? ni : 0.0f;
