@@ -54,7 +54,7 @@ HEADLINE_TRAFFIC = {("f32", "ray"): (378.6e6, "grid", "0c0a5d412e604041")}
 DCT_STOCH_LINEAR_TRAFFIC = (412.2e6, "tex2d", "37b3221bb3f3062a")
 # the EWA workload's stochastic kernel at max anisotropy 8 (24-byte records
 # in, 16-byte results out, one texel of the pyramid per lookup)
-EWA_STOCH_TRAFFIC = (536.7e6, "ewa", "b2bff40dab0dc65f")
+EWA_STOCH_TRAFFIC = (536.7e6, "ewa", "5c174c9909613a76")
 # the Gaussian workload's FIS draw at sigma 0.5 on the DCT set (uv in, 9
 # results out, block lines mostly cache-resident)
 GAUSS_FIS_TRAFFIC = (416.4e6, "tex2d", "37b3221bb3f3062a")

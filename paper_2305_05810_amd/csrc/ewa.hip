@@ -69,11 +69,14 @@ __device__ __forceinline__ int clampi(int v, int hi)
 template <int FMT, int C>
 __device__ __forceinline__ void texel(const TexLevel& L, int x, int y, float (&v)[C])
 {
-    const int64_t e = ((int64_t)clampi(y, L.h - 1) * L.w + clampi(x, L.w - 1)) * (C * fmt_bytes(FMT));
-    TexelRun<FMT, C> t;
-    t.load(static_cast<const char*>(L.texels) + e);
+    const int64_t e = ((int64_t)clampi(y, L.h - 1) * L.w + clampi(x, L.w - 1)) * C;
+    if constexpr (FMT == F32 && C == 4) {
+        const float4 f = reinterpret_cast<const float4*>(L.texels)[e >> 2];
+        v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+    } else {
 #pragma unroll
-    for (int c = 0; c < C; ++c) v[c] = t.value(c);
+        for (int c = 0; c < C; ++c) v[c] = load_texel<FMT>(L.texels, e + c);
+    }
 }
 
 // The ellipse of one level in texel units: coefficients and bounding box.
