@@ -611,10 +611,10 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
             __syncthreads();
         }
     }
-    const DctAxisPair px = dct_axis_pair<NT>(cosines, cx, W1, wx);
-    const DctAxisPair py = dct_axis_pair<NT>(cosines, cy, H1, wy);
-    // the kind's scale (36, 4 or 324 over both axes) divided out once per row of blocks
-    constexpr float inv = KIND == KIND_GAUSS_MEAN ? 1.0f : 1.0f / (axis_scale<KIND>() * axis_scale<KIND>());
+    // the weights of an axis add up to the kind's scale (the mean's are normalised)
+    constexpr float total = KIND == KIND_GAUSS_MEAN ? 1.0f : axis_scale<KIND>();
+    const DctAxisPair px = dct_axis_pair<NT>(cosines, cx, W1, wx, total);
+    const DctAxisPair py = dct_axis_pair<NT>(cosines, cy, H1, wy, total);
     float acc[CAP];
 #pragma unroll
     for (int c = 0; c < CAP; ++c) acc[c] = 0.0f;
@@ -631,12 +631,10 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
         uint4 w0[CAP / 4], w1[CAP / 4];
         dct_load_words(S, px.blk0, py.blk0, w0);
         if (more) dct_load_words(S, px.blk1, sx ? py.blk0 : py.blk1, w1);
-        const DctRow r0 = dct_row({py.a0.s0 * inv, py.a0.s1 * inv, py.a0.s2 * inv});
-        const DctRow r1 = dct_row({py.a1.s0 * inv, py.a1.s1 * inv, py.a1.s2 * inv});
+        const DctRow r0 = dct_row(py.a0), r1 = dct_row(py.a1);
         dct_add_words<CAP>(w0, dct_factors(r0, px.a0), C, acc);
         if (more) {
-            const DctRow r = {sx ? r0.dc : r1.dc, sx ? r0.k0 : r1.k0, sx ? r0.k1 : r1.k1, sx ? r0.k2 : r1.k2,
-                              sx ? r0.k11 : r1.k11};
+            const DctRow r = {sx ? r0.t0 : r1.t0, sx ? r0.t1 : r1.t1, sx ? r0.t2 : r1.t2, sx ? r0.r1 : r1.r1};
             const DctAxis a = {sx ? px.a1.s0 : px.a0.s0, sx ? px.a1.s1 : px.a0.s1, sx ? px.a1.s2 : px.a0.s2};
             dct_add_words<CAP>(w1, dct_factors(r, a), C, acc);
             if (use && sx && sy) {
@@ -651,8 +649,7 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
         const int nv = __any(use && py.blk1 != py.blk0) ? 2 : 1, nu = __any(use && px.blk1 != px.blk0) ? 2 : 1;
 #pragma unroll 1
         for (int v = 0; v < nv; ++v) {
-            const DctRow row = dct_row({(v ? py.a1.s0 : py.a0.s0) * inv, (v ? py.a1.s1 : py.a0.s1) * inv,
-                                        (v ? py.a1.s2 : py.a0.s2) * inv});
+            const DctRow row = dct_row({v ? py.a1.s0 : py.a0.s0, v ? py.a1.s1 : py.a0.s1, v ? py.a1.s2 : py.a0.s2});
             const int by = v ? py.blk1 : py.blk0;
 #pragma unroll 1
             for (int u = 0; u < nu; ++u) {
@@ -689,7 +686,7 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
         }
     }
 #pragma unroll
-    for (int c = 0; c < CAP; ++c) acc[c] = ok ? acc[c] : __builtin_nanf("");
+    for (int c = 0; c < CAP; ++c) acc[c] = ok ? dct_unscale<(int)(total * total)>(acc[c]) : __builtin_nanf("");
     if constexpr (STAGE) __syncthreads();   // every thread is done with the tile: it now stages the results
     block_store_via(S, out, n, live, oi, acc, order && scatter, tile);
 }
@@ -1007,11 +1004,13 @@ __global__ __launch_bounds__(BLOCK) void k_dct_gauss_mean(DctSrc<CAP> S, const f
         double p = gauss_phi(((double)x0 - xe - 0.5) / sg);
         for (int k = 0; __any(k < nt);) {
             DctAxis a = {0.0f, 0.0f, 0.0f};
+            const double first = p;
             for (int b = clampi(x0 + k, W1) >> 3; k < nt && clampi(x0 + k, W1) >> 3 == b; ++k) {
                 const double e = gauss_phi(((double)(x0 + k) - xe + 0.5) / sg);
                 dct_axis_add(a, cosines, clampi(x0 + k, W1), (float)(e - p));
                 p = e;
             }
+            a.s0 = (float)(p - first);   // the differences' sum, rounded once
             sums[(3 * nbx) * BLOCK + threadIdx.x] = a.s0;   // (a lane that is done writes zeros, at most
             sums[(3 * nbx + 1) * BLOCK + threadIdx.x] = a.s1;   // as many rows as the widest lane)
             sums[(3 * nbx + 2) * BLOCK + threadIdx.x] = a.s2;
@@ -1026,11 +1025,13 @@ __global__ __launch_bounds__(BLOCK) void k_dct_gauss_mean(DctSrc<CAP> S, const f
     for (int k = 0; __any(k < nt);) {
         DctAxis a = {0.0f, 0.0f, 0.0f};
         const int by = clampi(y0 + k, H1) >> 3;
+        const double first = p;
         for (; k < nt && clampi(y0 + k, H1) >> 3 == by; ++k) {
             const double e = gauss_phi(((double)(y0 + k) - ye + 0.5) / sg);
             dct_axis_add(a, cosines, clampi(y0 + k, H1), (float)(e - p));
             p = e;
         }
+        a.s0 = (float)(p - first);
         const DctRow row = dct_row(a);
         for (int u = 0; u < nbx; ++u) {   // the same count in every lane of the wave
             const float* e = sums + 3 * u * BLOCK + threadIdx.x;
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(BLOCK) void k_dct_gauss_mean(DctSrc<CAP> S, const f
         }
     }
 #pragma unroll
-    for (int c = 0; c < CAP; ++c) acc[c] = ok ? acc[c] : __builtin_nanf("");
+    for (int c = 0; c < CAP; ++c) acc[c] = ok ? dct_unscale<1>(acc[c]) : __builtin_nanf("");
     __syncthreads();   // the LDS rows now stage the results
     block_store_via(S, out, n, live, (int64_t)i0, acc, false, sums);
 }
