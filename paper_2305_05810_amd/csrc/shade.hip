@@ -11,6 +11,7 @@
 #include <math.h>
 
 #include "device_common.h"
+#include "shade_grid.h"
 #include "stf_internal.h"
 
 using namespace stf;
@@ -311,19 +312,23 @@ hipError_t launch_shade_f(const Levels& L, const float* q, int32_t n, int mode, 
                           int32_t* idx, hipStream_t s)
 {
     const dim3 block(BLOCK);
-    const int per = BLOCK / (CUBIC ? 4 : 2);
-    const dim3 one((unsigned)(((int64_t)n + BLOCK - 1) / BLOCK)), taps((unsigned)(((int64_t)n + per - 1) / per));
-    switch (mode) {
-    case STF_SHADE_AFTER_FILTER:
-        hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_SHADE_AFTER_FILTER>), taps, block, 0, s, L, q, n, out);
-        break;
-    case STF_FILTER_AFTER_SHADE:
-        hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_FILTER_AFTER_SHADE>), taps, block, 0, s, L, q, n, out);
-        break;
-    default:
-        hipLaunchKernelGGL((k_shade_one<CUBIC>), one, block, 0, s, L, q, n, key, out, idx);
+    if (mode != STF_SHADE_AFTER_FILTER && mode != STF_FILTER_AFTER_SHADE) {
+        hipLaunchKernelGGL((k_shade_one<CUBIC>), dim3(shade_blocks(n, 1, BLOCK)), block, 0, s, L, q, n, key, out, idx);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    for (int64_t first = 0; first < n; first += SHADE_PART) {
+        const int32_t m = (int32_t)shade_part(n, first);
+        const dim3 grid(shade_blocks(m, CUBIC ? 4 : 2, BLOCK));
+        const float* qp = q + 9 * first;
+        float* op = out + 3 * first;
+        if (mode == STF_SHADE_AFTER_FILTER)
+            hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_SHADE_AFTER_FILTER>), grid, block, 0, s, L, qp, m, op);
+        else
+            hipLaunchKernelGGL((k_shade_taps<CUBIC, STF_FILTER_AFTER_SHADE>), grid, block, 0, s, L, qp, m, op);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace
