@@ -18,6 +18,7 @@
 #include "device_common.h"
 #include "interp.h"
 #include "stf_internal.h"
+#include "tap_block.h"
 
 using namespace stf;
 
@@ -700,7 +701,7 @@ __device__ __forceinline__ float det_wave(const GridView& g, const int (&base)[3
         // wave's do, a lane sums its own query (1M samples in the medium of a
         // 128^3 grid, steps of about half a voxel: 24.5 us, four lanes a query
         // 27.1 us; of a 256^3 grid: 34.1 and 28.0 us).
-        const int blk = (base[0] >> 2) + (base[1] >> 2) * 1021 + (base[2] >> 2) * 31397;
+        const int blk = (int)tap_block(base[0], base[1], base[2]);
         const int before = __builtin_amdgcn_update_dpp(~blk, blk, 0x111, 0xF, 0xF, false);   // row_shr:1
         const int shared = __popcll(__ballot(taps && blk == before));
         if (shared * 16 > count * 10) {
