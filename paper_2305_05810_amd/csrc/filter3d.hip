@@ -655,6 +655,13 @@ struct __attribute__((aligned(16))) DetSlot {
 };
 constexpr uint32_t NO_CHUNK = 0xffffffffu;
 
+// An unsorted call: 2^log_queries queries a wave; where more than shared16 in 16
+// of those that meet a leaf share their tap block with the one before, a lane
+// sums its own.
+struct DetPlan {
+    int log_queries, shared16;
+};
+
 // acc + v[y] w, v[y] being lane y's v of this lane's group of four.
 template <int Y>
 __device__ __forceinline__ float fma_quad(float v, float w, float acc)
@@ -682,7 +689,8 @@ __device__ __forceinline__ float fma_quad(float v, float w, float acc)
 // 97 us.
 template <int FMT, int KIND>
 __device__ __forceinline__ float det_wave(const GridView& g, const int (&base)[3], const float (&w)[3][4],
-                                          const int32_t (&leaf)[8], bool taps, DetSlot* __restrict__ S)
+                                          const int32_t (&leaf)[8], bool taps, const DetPlan& plan,
+                                          DetSlot* __restrict__ S)
 {
     constexpr int NT = 4;
     constexpr uint32_t TB = FMT == F32 ? 4u : (FMT == F16 || FMT == BF16 ? 2u : 1u);
@@ -700,11 +708,13 @@ __device__ __forceinline__ float det_wave(const GridView& g, const int (&base)[3
         // voxels share their accesses anyway: where more than 10 in 16 of the
         // wave's do, a lane sums its own query (1M samples in the medium of a
         // 128^3 grid, steps of about half a voxel: 24.5 us, four lanes a query
-        // 27.1 us; of a 256^3 grid: 34.1 and 28.0 us).
+        // 27.1 us; of a 256^3 grid: 34.1 and 28.0 us; fewer queries: det_plan).
         const int blk = (int)tap_block(base[0], base[1], base[2]);
         const int before = __builtin_amdgcn_update_dpp(~blk, blk, 0x111, 0xF, 0xF, false);   // row_shr:1
         const int shared = __popcll(__ballot(taps && blk == before));
-        if (shared * 16 > count * 10) {
+        // (one scalar: with two tests the binary32 way's loads are waited for one
+        // by one, 50,000 medium samples 7.0 instead of 5.6 us)
+        if (__builtin_amdgcn_readfirstlane((count > 32) & (shared * 16 > count * plan.shared16))) {
             if (taps) result = det_taps<FMT, KIND>(g, base, leaf, w);
             count = 0;
         } else if (taps) {
@@ -798,19 +808,21 @@ __device__ __forceinline__ float det_wave(const GridView& g, const int (&base)[3
 template <int FMT, int KIND>
 __global__ __launch_bounds__(BLOCK, 6) void k_grid_deterministic(
     GridView g, const float* __restrict__ q, int32_t n, float* __restrict__ out, const int32_t* __restrict__ order,
-    int scatter)
+    int scatter, DetPlan plan)
 {
     __shared__ DetSlot slots[BLOCK];
-    const int32_t i = blockIdx.x * BLOCK + threadIdx.x;
-    const bool live = i < n;
-    const int32_t src = live ? i : 0;
+    const int lane = threadIdx.x % 64;
+    const uint32_t own = ((blockIdx.x * (BLOCK / 64) + threadIdx.x / 64) << plan.log_queries) + lane;   // below 2^31 + 64
+    const bool live = (lane >> plan.log_queries) == 0 && own < (uint32_t)n;
+    const int32_t i = live ? (int32_t)own : 0;
+    const int32_t src = i;
     const float p[3] = {q[3 * (int64_t)src], q[3 * (int64_t)src + 1], q[3 * (int64_t)src + 2]};
     int base[3] = {0, 0, 0};
     float w[3][4];
     const bool ok = det_setup<KIND>(p, base, w);
     int32_t leaf[8];
     const bool taps = ok && live && det_leaves<KIND>(g, base, leaf);
-    float sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, slots + threadIdx.x / 64 * 64);
+    float sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, plan, slots + threadIdx.x / 64 * 64);
     if (!live) return;
     if (!taps) sum = det_background<KIND>(g, w);   // empty space
     __builtin_nontemporal_store(ok ? det_unscale<KIND>(sum) : __builtin_nanf(""),
@@ -1028,7 +1040,7 @@ __global__ __launch_bounds__(BLOCK, (STAGE_QUADS<FMT> ? 6 : 8)) void k_grid_det_
     } else {
         float sum = 0.0f;
         if constexpr (STAGE_QUADS<FMT>)
-            sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, reinterpret_cast<DetSlot*>(tile) + wave * 64);
+            sum = det_wave<FMT, KIND>(g, base, w, leaf, taps, {6, 10}, reinterpret_cast<DetSlot*>(tile) + wave * 64);
         else if (taps)
             sum = det_taps<FMT, KIND>(g, base, leaf, w);
         if (!live) return;
@@ -1098,6 +1110,30 @@ __global__ __launch_bounds__(BLOCK) void k_grid_moments(GridView g, const float*
     }
 }
 
+// How a call of n unsorted queries is divided.  Up to a block of 256 per CU
+// (65,536) the chip is not full and a wave's chain of instructions is the time
+// -- a round of 16 queries by four lanes each, or 64 taps by a lane each -- and
+// half a wave of queries has half the rounds; above it the work of the CUs is,
+// and sharing queries are the less work for a lane each the fewer waves wait
+// beside them.  Samples in the medium of the 512^3 and 256^3 grids (43 and 65
+// in 100 share their tap block with the one before), binary32, us, four lanes a
+// query (32 or 64 queries a wave) and a lane each:
+//     8,000:  4.4, 4.4 (32); 5.8, 5.7 (64); 5.0, 4.8
+//    50,000:  5.8, 5.7 (32); 6.3, 5.7 (64); 5.6, 5.0
+//   100,000:  8.2, 6.8 (64); 11.6, 6.0
+//   400,000: 21.2, 15.2 (64); 37.4, 17.2
+// and of binary16 at 70,000: 7.3; 6.4.  Whatever the plan, a query's bits are
+// the same.
+template <int FMT>
+DetPlan det_plan(int64_t n)
+{
+    if (n <= 24576) return {5, 10};
+    if (n <= (FMT == F32 ? 65536 : 98304)) return {6, -1};
+    if (n <= 131072) return {6, 8};
+    if (n <= 262144) return {6, FMT == F32 ? 9 : 8};
+    return {6, 10};
+}
+
 template <int FMT, int KIND>
 void launch3d_kind(const GridView& g, const float* q, int32_t n, int mode, uint32_t key, float* out, int32_t* idx,
                    const int32_t* order, int scatter, hipStream_t stream)
@@ -1129,8 +1165,12 @@ void launch3d_kind(const GridView& g, const float* q, int32_t n, int mode, uint3
         else if (order)   // a sorted stream: neighbouring queries share their 64 taps
             hipLaunchKernelGGL((k_grid_det_staged<FMT, KIND>), grid, block, 0, stream, g, q, n, out, order, scatter,
                                stage_counters());
-        else
-            hipLaunchKernelGGL((k_grid_deterministic<FMT, KIND>), grid, block, 0, stream, g, q, n, out, order, scatter);
+        else {
+            const DetPlan plan = det_plan<FMT>(n);
+            const int64_t per = (int64_t)(BLOCK / 64) << plan.log_queries;
+            hipLaunchKernelGGL((k_grid_deterministic<FMT, KIND>), dim3((unsigned)((n + per - 1) / per)), block, 0, stream,
+                               g, q, n, out, order, scatter, plan);
+        }
     }
 }
 
