@@ -125,15 +125,27 @@ __device__ __forceinline__ Texel decode_texel(uint2 t)
     return m;
 }
 
-// f^ from sums over the taps: of the lobes, and of the diffuse one times the
-// albedo codes.
-__device__ __forceinline__ void finish(const Frame& fr, const float (&codes)[3], float specular, float (&f)[3])
+// The taps' weights of an axis add up to this: cubic6's are six times the
+// B-spline's, and the scale goes with the constants at the end (a sixth rounded
+// in every weight is off by 3e-8 each time).
+template <bool CUBIC>
+constexpr double window_scale()
 {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const float d = codes[c] * (INV_PI / 255.0f);
-        f[c] = specular == 0.0f ? d : __builtin_fmaf(fr.ks, specular, d);   // ks has no value for opposite directions
-    }
+    return CUBIC ? 36.0 : 1.0;
+}
+
+// A channel of f^ from sums over the taps: of the diffuse lobe times the albedo
+// codes and of the specular one, or (ONE_SPECULAR) the specular lobe of the
+// filtered material.  1 / (255 pi) scales the codes in two parts: one part alone
+// is off by 5.2e-8, more than the rest of a matt value's rounding.
+template <bool CUBIC, bool ONE_SPECULAR>
+__device__ __forceinline__ float finish(const Frame& fr, float codes, float specular)
+{
+    constexpr double inv = 1.0 / (255.0 * 3.14159265358979323846 * window_scale<CUBIC>());
+    constexpr float hi = (float)inv, lo = (float)(inv - (double)hi);
+    const float d = __builtin_fmaf(codes, hi, codes * lo);
+    const float ks = ONE_SPECULAR || !CUBIC ? fr.ks : fr.ks * (float)(1.0 / window_scale<CUBIC>());
+    return specular == 0.0f ? d : __builtin_fmaf(ks, specular, d);   // ks has no value for opposite directions
 }
 
 __device__ __forceinline__ int clampi(int v, int hi)
@@ -234,8 +246,8 @@ __global__ __launch_bounds__(BLOCK) void k_shade_taps(Levels L, const float* __r
     int x0 = cx, y0 = cy;
     if constexpr (CUBIC) {
         const Cubic6 ca = cubic6(tx), cb = cubic6(ty);
-        wx = (a == 0 ? ca.a0 : a == 1 ? ca.a1 : a == 2 ? ca.a2 : ca.a3) * K6;
-        wy[0] = cb.a0 * K6; wy[1] = cb.a1 * K6; wy[2] = cb.a2 * K6; wy[3] = cb.a3 * K6;
+        wx = a == 0 ? ca.a0 : a == 1 ? ca.a1 : a == 2 ? ca.a2 : ca.a3;
+        wy[0] = cb.a0; wy[1] = cb.a1; wy[2] = cb.a2; wy[3] = cb.a3;
         x0 -= 1;
         y0 -= 1;
     } else {
@@ -270,22 +282,22 @@ __global__ __launch_bounds__(BLOCK) void k_shade_taps(Levels L, const float* __r
     for (int c = 0; c < 3; ++c) codes[c] = lane_sum<NT>(codes[c]);
     if constexpr (MODE == STF_SHADE_AFTER_FILTER) {
         float d;
-        lobes(fr, lane_sum<NT>(nx), lane_sum<NT>(ny), lane_sum<NT>(rough), d, spec);
+        constexpr float inv = (float)(1.0 / window_scale<CUBIC>());
+        lobes(fr, lane_sum<NT>(nx) * inv, lane_sum<NT>(ny) * inv, lane_sum<NT>(rough) * inv, d, spec);
 #pragma unroll
         for (int c = 0; c < 3; ++c) codes[c] *= d;
     } else {
         spec = lane_sum<NT>(spec);
     }
-    float f[3];
-    finish(fr, codes, spec, f);
-    if (!ok) f[0] = f[1] = f[2] = __builtin_nanf("");
     float* o = out + 3 * (int64_t)i;   // results are streamed out (nontemporal stores)
+    auto put = [&](int c, float code) {
+        __builtin_nontemporal_store(ok ? finish<CUBIC, MODE == STF_SHADE_AFTER_FILTER>(fr, code, spec) : __builtin_nanf(""), o + c);
+    };
     if constexpr (CUBIC) {
-        const float mine = a == 0 ? f[0] : a == 1 ? f[1] : f[2];
-        if (a < 3) __builtin_nontemporal_store(mine, o + a);
+        if (a < 3) put(a, a == 0 ? codes[0] : a == 1 ? codes[1] : codes[2]);
     } else {
-        __builtin_nontemporal_store(a ? f[1] : f[0], o + a);
-        if (a) __builtin_nontemporal_store(f[2], o + 2);
+        put(a, a ? codes[1] : codes[0]);
+        if (a) put(2, codes[2]);
     }
 }
 
@@ -330,8 +342,8 @@ __global__ __launch_bounds__(BLOCK) void k_shade_lane(Levels L, const float* __r
     float wx[NT], wy[NT];
     if constexpr (CUBIC) {
         const Cubic6 ca = cubic6(tx), cb = cubic6(ty);
-        wx[0] = ca.a0 * K6; wx[1] = ca.a1 * K6; wx[2] = ca.a2 * K6; wx[3] = ca.a3 * K6;
-        wy[0] = cb.a0 * K6; wy[1] = cb.a1 * K6; wy[2] = cb.a2 * K6; wy[3] = cb.a3 * K6;
+        wx[0] = ca.a0; wx[1] = ca.a1; wx[2] = ca.a2; wx[3] = ca.a3;
+        wy[0] = cb.a0; wy[1] = cb.a1; wy[2] = cb.a2; wy[3] = cb.a3;
         cx -= 1;
         cy -= 1;
     } else {
@@ -419,17 +431,16 @@ __global__ __launch_bounds__(BLOCK) void k_shade_lane(Levels L, const float* __r
     float codes[3] = {sum[0], sum[1], sum[2]}, spec = sum[3];
     if constexpr (AFTER) {
         float d;
-        lobes(fr, sum[4], sum[5], sum[3], d, spec);
+        constexpr float inv = (float)(1.0 / window_scale<CUBIC>());
+        lobes(fr, sum[4] * inv, sum[5] * inv, sum[3] * inv, d, spec);
 #pragma unroll
         for (int c = 0; c < 3; ++c) codes[c] *= d;
     }
-    float f[3];
-    finish(fr, codes, spec, f);
-    if (!ok) f[0] = f[1] = f[2] = __builtin_nanf("");
     if (!live) return;
     float* o = out + 3 * i;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(f[c], o + c);
+    for (int c = 0; c < 3; ++c)
+        __builtin_nontemporal_store(ok ? finish<CUBIC, AFTER>(fr, codes[c], spec) : __builtin_nanf(""), o + c);
 }
 
 // One tap, chosen at random, is shaded.
@@ -474,10 +485,9 @@ __global__ __launch_bounds__(BLOCK) void k_shade_one(Levels L, const float* __re
     const Texel m = decode_texel(texel);
     float d, sp;
     lobes(fr, m.nx, m.ny, m.rough, d, sp);
-    const float c[3] = {d * m.albedo[0], d * m.albedo[1], d * m.albedo[2]};
     float f[3];
-    finish(fr, c, sp, f);
-    if (!ok) f[0] = f[1] = f[2] = __builtin_nanf("");
+#pragma unroll
+    for (int c = 0; c < 3; ++c) f[c] = ok ? finish<false, true>(fr, d * m.albedo[c], sp) : __builtin_nanf("");
     if (idx) {
         idx[3 * (int64_t)i] = ok ? sx : BAD_INDEX;
         idx[3 * (int64_t)i + 1] = ok ? sy : BAD_INDEX;
