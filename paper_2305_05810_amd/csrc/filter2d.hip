@@ -691,6 +691,59 @@ __global__ __launch_bounds__(BLOCK) void k_dct_det(DctSrc<CAP> S, const float* _
     block_store_via(S, out, n, live, oi, acc, order && scatter, tile);
 }
 
+// Bilinear filtering of a DCT texture in small calls, a thread per query and
+// group of four channels: with all channels in one thread the chain of its up to
+// four blocks is the time of a call that leaves most of the chip idle.  The
+// sums are those of k_dct_det, in its order: the same bits.  1,000 scattered
+// queries of 16 channels: 5.7 us decoding each tap, 7.9 with a thread per query,
+// 3.0 so; 60,000 of 9: 5.3, 5.0, 4.2; 200,000 in a frame: 8.7, 5.9, 7.9, hence
+// the line.
+constexpr int64_t DCT_GROUPS_TO = 65536;   // a block of queries per CU
+
+template <int CAP>
+__global__ __launch_bounds__(BLOCK) void k_dct_linear_groups(DctSrc<CAP> S, const float* __restrict__ q, int32_t n,
+                                                             float* __restrict__ out, const int32_t* __restrict__ order,
+                                                             int scatter)
+{
+    constexpr int G = CAP / 4;
+    __shared__ float2 cosines[8];
+    dct_fill_cosines(cosines);
+    __syncthreads();
+    const int32_t t = blockIdx.x * BLOCK + threadIdx.x, i = t / G, g = t % G;   // t < 4 DCT_GROUPS_TO + BLOCK
+    const int left = S.channels() - 4 * g;
+    if (i >= n || left <= 0) return;
+    const float2 uv = reinterpret_cast<const float2*>(q)[i];
+    int cx = 0, cy = 0;
+    float tx = 0.0f, ty = 0.0f;
+    const bool ok = cell_of(uv.x * (float)S.w() - 0.5f, cx, tx) & cell_of(uv.y * (float)S.h() - 0.5f, cy, ty);
+    float wx[4], wy[4];
+    cx += axis_weights_scaled<KIND_LINEAR>(tx, wx);
+    cy += axis_weights_scaled<KIND_LINEAR>(ty, wy);
+    const DctAxisPair px = dct_axis_pair<2>(cosines, cx, S.w() - 1, wx, 1.0f);
+    const DctAxisPair py = dct_axis_pair<2>(cosines, cy, S.h() - 1, wy, 1.0f);
+    const bool sx = px.blk1 != px.blk0, sy = py.blk1 != py.blk0;
+    auto words = [&](int bx, int by) {
+        return reinterpret_cast<const uint4*>(S.blocks + ((int64_t)by * S.BW + bx) * CAP)[g];
+    };
+    // a lane without a second, third or fourth block asks for its first again
+    const uint4 w0 = words(px.blk0, py.blk0), w1 = words(px.blk1, sx ? py.blk0 : py.blk1),
+                w2 = words(px.blk0, py.blk1), w3 = words(px.blk1, py.blk1);
+    const DctRow r0 = dct_row(py.a0), r1 = dct_row(py.a1);
+    float4 acc = dct_add_group(w0, dct_factors(r0, px.a0), left, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
+    const DctRow r = {sx ? r0.t0 : r1.t0, sx ? r0.t1 : r1.t1, sx ? r0.t2 : r1.t2, sx ? r0.r1 : r1.r1};
+    const DctAxis a = {sx ? px.a1.s0 : px.a0.s0, sx ? px.a1.s1 : px.a0.s1, sx ? px.a1.s2 : px.a0.s2};
+    acc = dct_add_group(w1, dct_factors(r, a), left, acc);
+    if (sx && sy) {
+        acc = dct_add_group(w2, dct_factors(r1, px.a0), left, acc);
+        acc = dct_add_group(w3, dct_factors(r1, px.a1), left, acc);
+    }
+    const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+    float* o = out + ((order && scatter) ? (int64_t)order[i] : (int64_t)i) * S.channels() + 4 * g;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (c < left) o[c] = ok ? dct_unscale<1>(v[c]) : __builtin_nanf("");
+}
+
 // channel-0 moments of the stochastic estimator over many seeds
 template <class Src, int KIND>
 __global__ __launch_bounds__(BLOCK) void k_tex2d_moments(Src S, const float* __restrict__ q, int32_t n,
@@ -1076,6 +1129,12 @@ void launch2d_kind(const Src& S, const float* q, int32_t n, int mode, uint32_t k
             hipLaunchKernelGGL((k_tex2d_stochastic<Src, KIND == KIND_BSPLINE, true>), grid, block, 0, stream, S, q, n,
                                key, out, idx, order, scatter);
     } else {
+        if constexpr (Src::DECODES && KIND == KIND_LINEAR && Src::CAP > 4)
+            if (n <= DCT_GROUPS_TO) {
+                hipLaunchKernelGGL((k_dct_linear_groups<Src::CAP>), dim3((unsigned)((n * (Src::CAP / 4) + BLOCK - 1) / BLOCK)),
+                                   block, 0, stream, S, q, n, out, order, scatter);
+                return;
+            }
         if constexpr (Src::DECODES)   // by blocks; bilinear windows (2x2) share too little to stage
             hipLaunchKernelGGL((k_dct_det<Src::CAP, KIND, KIND != KIND_LINEAR>), grid, block, 0, stream, S, q, n, out,
                                order, scatter, KIND != KIND_LINEAR ? stage_counters() : nullptr, 0.0f);
