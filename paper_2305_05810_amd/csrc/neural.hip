@@ -858,9 +858,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // registers for the whole loop they would not leave room for three waves.
     __shared__ f32x16 C2s[2][2];
     __shared__ f32x4 C3s[2];
-    if (threadIdx.x < 64) reinterpret_cast<float*>(C2s)[threadIdx.x] = reinterpret_cast<const float*>(pk->b2)[threadIdx.x];
-    if (threadIdx.x < NO) reinterpret_cast<float*>(C3s)[threadIdx.x] = reinterpret_cast<const float*>(pk->b3)[threadIdx.x];
-    __syncthreads();
+    // The wave's first query, the biases and the operand images are asked for
+    // together, not one after the other's barrier: 0.1 to 0.2 us of the 3.6 that
+    // a small stochastic call takes.
+    const int32_t npair = (int32_t)(((int64_t)a.n + QPP - 1) / QPP);
+    const uint32_t nq = (uint32_t)a.n;
+    auto load_uv = [&](int32_t p) {   // past the end: the last query
+        return reinterpret_cast<const float2*>(a.q)[min((uint32_t)p * QPP + lane / TAPS, nq - 1)];
+    };
+    float2 uv_first = make_float2(0.0f, 0.0f);
+    if constexpr (TAPS != 16) uv_first = load_uv(min(wave, npair));
+    const float c2 = threadIdx.x < 64 ? reinterpret_cast<const float*>(pk->b2)[threadIdx.x] : 0.0f;
+    const float c3 = threadIdx.x < NO ? reinterpret_cast<const float*>(pk->b3)[threadIdx.x] : 0.0f;
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
         A1[mb] = pk->a1[mb][lane];
@@ -868,12 +877,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) A2[mb][kb] = pk->a2[mb][kb][lane];
     }
+    if (threadIdx.x < 64) reinterpret_cast<float*>(C2s)[threadIdx.x] = c2;
+    if (threadIdx.x < NO) reinterpret_cast<float*>(C3s)[threadIdx.x] = c3;
+    __syncthreads();
     // The bias ones as every lane's slots j = 0..2 hold them in the upper
     // half: (1, 1, 1, 0, 0, 0, 0, 0) in bf16, as four 32-bit words.
     const uint32_t ONE_WORDS[4] = {0x3F803F80u, 0x00003F80u, 0u, 0u};
 
-    const int32_t npair = (int32_t)(((int64_t)a.n + QPP - 1) / QPP);
-    const uint32_t nq = (uint32_t)a.n;
     const uint4* L = reinterpret_cast<const uint4*>(a.quad16);
 
     // A pair's decode of this lane, its latents in flight.  Every lane loads:
@@ -991,9 +1001,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         // While pair i runs its MFMAs, the latents of pair i + 1 and the
         // queries of pair i + 2 are in flight; two pairs a turn, so that the
         // stages swap without moves.
-        auto load_uv = [&](int32_t p) {   // past the end: the last query
-            return reinterpret_cast<const float2*>(a.q)[min((uint32_t)p * QPP + lane / TAPS, nq - 1)];
-        };
         auto stage = [&](int32_t p, float2 uv, Stage& st) {
             const Decode d = locate<CUBIC, STOCH>(a, (uint32_t)p * QPP + lane / TAPS, lane % TAPS, uv);
             st.w = d.fin ? d.w : __builtin_nanf("");
@@ -1005,7 +1012,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         };
         int32_t p = wave;
         if (p >= npair) return;
-        stage(p, load_uv(p), S0);
+        stage(p, uv_first, S0);
         float2 uv_next = load_uv(min(p + nwaves, npair));
         auto turn = [&](const Stage& cur, Stage& nxt) {
             const float2 uv_after = load_uv(min(p + 2 * nwaves, npair));
@@ -1411,6 +1418,10 @@ stf_status stf_ntex_filter(const stf_neural* nt, const float* queries_dev, int64
     // Persistent waves, one resident set (3 per SIMD on 256 CUs): the weights
     // load once per wave.
     int64_t waves = pairs < 3072 ? pairs : 3072;
+    // The 16-tap kernel's waves take two pairs a turn where there are more than
+    // waves: up to two sets a wave a pair, which leaves no SIMD with six of them
+    // while others have three (20,000 queries 8.5 us, 7.9 so).
+    if (taps == 16 && pairs <= 2 * 3072) waves = pairs;
     dim3 grid((unsigned)((waves + 3) / 4)), block(256);
     hipStream_t st = (hipStream_t)hip_stream;
     bool cubic = filter == STF_CUBIC_BSPLINE;
