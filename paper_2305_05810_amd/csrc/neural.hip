@@ -441,17 +441,25 @@ struct UpdateArgs {
 // gradient they consumed.  Bound by memory (32 bytes moved per latent); two
 // sums and two steps took four launches and 32 us a step, of which this takes
 // 12 (512^2 latents).
+//
+// STREAMED: the moments go past the caches, for latents whose four arrays the
+// 256 MB behind the L2s cannot hold from step to step (2048^2: 204 us a step of
+// 16 samples in two launches, 210 in one, 140 so; 512^2, which they hold: 16.7
+// and 18.4).
+constexpr int64_t STREAM_FROM = (int64_t)1 << 24;   // latent values, 16 bytes each
 constexpr int RGROUP = 32;
 constexpr int UBLOCK = 512, UWAVES = UBLOCK / 64;
 constexpr int UPDATE_MLP = (PSTRIDE + 63) / 64;
 
+template <bool STREAMED>
 __global__ __launch_bounds__(UBLOCK) void k_ntex_update(UpdateArgs a)
 {
     if (blockIdx.x >= UPDATE_MLP) {
         const int32_t e = (int32_t)(blockIdx.x - UPDATE_MLP) * UBLOCK + (int32_t)threadIdx.x;
         if (e >= a.nlat4) return;
-        f32x4 p = reinterpret_cast<f32x4*>(a.lat)[e], m = reinterpret_cast<f32x4*>(a.m_lat)[e],
-              v = reinterpret_cast<f32x4*>(a.v_lat)[e];
+        f32x4 *pm = reinterpret_cast<f32x4*>(a.m_lat) + e, *pv = reinterpret_cast<f32x4*>(a.v_lat) + e;
+        f32x4 p = reinterpret_cast<f32x4*>(a.lat)[e], m = STREAMED ? __builtin_nontemporal_load(pm) : *pm,
+              v = STREAMED ? __builtin_nontemporal_load(pv) : *pv;
         const f32x4 g = reinterpret_cast<f32x4*>(a.g_lat)[e];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -462,8 +470,13 @@ __global__ __launch_bounds__(UBLOCK) void k_ntex_update(UpdateArgs a)
             v[k] = vk;
         }
         reinterpret_cast<f32x4*>(a.lat)[e] = p;
-        reinterpret_cast<f32x4*>(a.m_lat)[e] = m;
-        reinterpret_cast<f32x4*>(a.v_lat)[e] = v;
+        if constexpr (STREAMED) {
+            __builtin_nontemporal_store(m, pm);
+            __builtin_nontemporal_store(v, pv);
+        } else {
+            *pm = m;
+            *pv = v;
+        }
         reinterpret_cast<f32x4*>(a.g_lat)[e] = (f32x4)0.0f;
         return;
     }
@@ -1196,8 +1209,9 @@ hipError_t run_update(stf_neural* nt, int32_t blocks, int32_t B, float* loss, bo
         a.c1 = c1;
         a.c2 = c2;
     }
-    hipLaunchKernelGGL(k_ntex_update, dim3((unsigned)(UPDATE_MLP + (a.nlat4 + UBLOCK - 1) / UBLOCK)), dim3(UBLOCK), 0, s,
-                       a);
+    const dim3 grid((unsigned)(UPDATE_MLP + (a.nlat4 + UBLOCK - 1) / UBLOCK)), block(UBLOCK);
+    if (nlat(nt) >= STREAM_FROM) hipLaunchKernelGGL(k_ntex_update<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(k_ntex_update<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
