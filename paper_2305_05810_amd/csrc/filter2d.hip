@@ -492,8 +492,8 @@ __device__ __forceinline__ void dct_add_words(const uint4 (&w4)[CAP / 4], const 
 // Bound by VALU issue (weight sums and the multiply-adds; the streams alone
 // would take 75 us of the frame below).  4K frame of a 4096^2 set of 9
 // channels, 16 taps: 507 us with each texel of the taps' box decoded into
-// LDS once, 124 us so; 2M uniform uv: 228 us decoding every tap, 106 us so;
-// 4 taps, 4 channels, 2M pixels of a frame: 20.9 and 15.2 us.  An unguarded
+// LDS once, 124 us so (128 as the sums are rounded now); 2M uniform uv: 228 us
+// decoding every tap, 106 us so; 4 taps, 4 channels, 2M pixels of a frame: 20.9 and 15.2 us.  An unguarded
 // group of four channels lets its LDS reads overlap (a test per channel: 141
 // us); tiles of 16, 20 and 32 KiB: 127, 124 and 147 us (the last one leaves 4
 // blocks per CU).

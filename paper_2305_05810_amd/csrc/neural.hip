@@ -219,8 +219,8 @@ __device__ __forceinline__ f32x4 mask4(f32x4 v, const f32x4& h)   // v where h >
 // from the same LDS matrices with the sample in the k-slot, 4 bytes a lane,
 // and each tile's sum, formed from zero, is added to the wave's registers.
 //
-// 600 matrix instructions of 32 cycles per tile would take 64 us for 262,144
-// samples on 1,024 SIMDs; the chain of seven barriers per tile, each with an
+// 576 matrix instructions of 32 cycles per tile would take 61 us for 262,144
+// samples on 1,024 SIMDs; the chain of six barriers per tile, each with an
 // LDS round trip and a dependent chain, holds the pass at 107 us.  Four waves
 // per SIMD from two blocks per CU fill each other's gaps, and a tile's gathers
 // are issued a tile ahead.  The products that not all waves share (the output,
@@ -821,7 +821,8 @@ __device__ __forceinline__ float keep_sum(float a, float b, bool odd)
 
 // The 16-tap sums of both batches of a pair (a row of 16 lanes holds a query's
 // taps): the eight values a lane holds are halved at each step with the lanes
-// that share their sum, 14 additions instead of 32.  Lane l (of those with
+// that share their sum, 8 additions (each with a lane move and two selects
+// before it) instead of 32.  Lane l (of those with
 // l / 4 even) ends with channel 4 (l / 16 % 2) + l % 4 of query
 // 2 (l / 8 % 2) + l / 32 of the pair's four, 128 contiguous bytes per wave.
 __device__ __forceinline__ void emit16(const InferArgs& a, const f32x4 (&D3)[2], const float (&w)[2], uint32_t q0,
